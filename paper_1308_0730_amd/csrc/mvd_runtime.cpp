@@ -389,8 +389,11 @@ bool cfg_fits(const mvd_handle* h, int kind, int c);
 int pick_cfg(const mvd_handle* h, int kind) {
   if (h->force_cfg > 0 && cfg_fits(h, kind, h->force_cfg - 1)) return h->force_cfg - 1;
   const int nrt = mvd_exact_cfg(kind) - mvd_ct_num_cfgs(kind);
-  // compile-time candidates in order of preference
-  static const int ct_x[] = {0, 3, 4, 5, 6};
+  // compile-time candidates in order of preference (rows of 256 points: two
+  // per wave with radices 8, 8, 4; four with 16, 16 hold twice the operands
+  // in registers, on 512x512x256 with weights 163 and 243 us per ratio and
+  // update pass against 146 and 230)
+  static const int ct_x[] = {1, 3, 4, 5, 6};
   static const int ct_c[] = {0, 3, 6, 7};
   if (kind == PASS_X) {
     for (int c : ct_x)
