@@ -114,7 +114,8 @@ typedef void (*mvd_free_fn)(void* ptr, void* ctx);
  *   alloc/free device allocator and its context (NULL = hipMalloc/hipFree);
  *              alloc returns NULL on failure, and must return 256-byte aligned memory
  *   use_graphs 0 = launch kernels directly, 1 = replay one HIP graph per
- *              iteration (default when options are NULL)
+ *              iteration (default when options are NULL; handles whose
+ *              blocks have different extents launch directly)
  *   tile_config  0 = autotuned/default pass shapes; k > 0 forces candidate k-1
  *   boundary   MVD_BOUNDARY_CIRCULAR (0): the volume is one period of a
  *              periodic grid (the convolutions wrap around);
@@ -315,11 +316,20 @@ int mvd_set_psfs(mvd_handle* h, const float* const* psfs, const int* psf_dims, i
  * out[0..cap), the candidates for transforms of length max_len and returns
  * how many exist.  mvd_set_tiles selects one candidate per kind for a handle
  * (MVD_EINVAL if one does not fit its volumes); later iterations use them.
- * mvd_get_tiles reports the current choice. */
+ * mvd_get_tiles reports the current choice.
+ *
+ * Until shapes are set, a handle may run its convolutions in two passes over
+ * memory instead of four (volumes up to about 10 million voxels: one
+ * workgroup takes a whole (y, z) plane of the spectrum), which needs the
+ * kernels' full spectra (4 bytes per voxel, view and kernel kind, allocated
+ * on first use; without that memory the four passes run).  The shapes belong
+ * to the four passes: mvd_set_tiles selects them, mvd_profile times them, and
+ * mvd_default_tiles takes a handle back to its shapes and form at create. */
 int mvd_tile_candidates(int kind, int max_len, int* out, int cap);
 int mvd_tile_shape(int kind, int cfg, int* threads, int* per_tile, int* max_len, int* exact_len);
 int mvd_set_tiles(mvd_handle* h, int cfg_x, int cfg_y, int cfg_z);
 int mvd_get_tiles(const mvd_handle* h, int* cfg);
+int mvd_default_tiles(mvd_handle* h);
 
 /* Schedule of a multi-block handle's runs (the autotuner's other knob).
  * Blocks are independent, so every schedule gives the same results; they

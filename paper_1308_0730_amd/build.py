@@ -35,6 +35,10 @@ SOURCES = [
     ("mvd_exact_x.hip", True),
     ("mvd_exact_y.hip", True),
     ("mvd_kernels_ct.hip", True),
+    ("mvd_tp_x.hip", True),
+    ("mvd_tp_x_update.hip", True),
+    ("mvd_tp_x_comb.hip", True),
+    ("mvd_tp_plane.hip", True),
     ("mvd_weights.hip", True),
     ("mvd_embed.hip", True),
     ("mvd_runtime.cpp", True),

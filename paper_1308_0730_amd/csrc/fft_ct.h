@@ -139,6 +139,47 @@ struct Dft<20, INV> : DftPQ<4, 5, INV> {};
 template <bool INV>
 struct Dft<25, INV> : DftPQ<5, 5, INV> {};
 
+// n / D for 0 <= n <= MAXN.  The plain operator on an int of unknown sign and
+// range costs quarter-rate 32-bit products and sign fixes; with the range
+// known at compile time one 24-bit product and a shift are exact.
+template <int D, int MAXN>
+struct DivC {
+  static constexpr int shift() {
+    for (int s = 1; s <= 30; ++s) {
+      const unsigned long long p = 1ull << s, m = (p + D - 1) / D, e = m * D - p;
+      if (m < (1ull << 24) && (unsigned long long)MAXN * m < (1ull << 32) && (unsigned long long)(MAXN + 1) * e < p)
+        return s;
+    }
+    return -1;
+  }
+  static constexpr int S = shift();
+  static_assert(MAXN < (1 << 24) && S > 0, "no exact 24-bit reciprocal");
+  static __device__ __forceinline__ int div(int n) {
+    if constexpr ((D & (D - 1)) == 0) {
+      return (int)((unsigned)n >> __builtin_ctz(D));
+    } else {
+      constexpr unsigned m = (unsigned)(((1ull << S) + D - 1) / D);
+      return (int)(__umul24((unsigned)n, m) >> S);
+    }
+  }
+  static __device__ __forceinline__ int mod(int n) {
+    if constexpr ((D & (D - 1)) == 0) return n & (D - 1);
+    return n - (int)__umul24((unsigned)div(n), D);
+  }
+};
+
+// Line and butterfly of work item `it` (< NL * NB rounded up to whole rounds).
+template <int NL, int NB, int MAXIT, bool LF>
+__device__ __forceinline__ void item_of(int it, int& line, int& j) {
+  if constexpr (LF) {
+    line = DivC<NL, MAXIT>::mod(it);
+    j = DivC<NL, MAXIT>::div(it);
+  } else {
+    line = DivC<NB, MAXIT>::div(it);
+    j = it - (int)__umul24((unsigned)line, NB);
+  }
+}
+
 // Accessor adaptors: the five-argument store used by the compile-time stages.
 template <class A>
 struct Plain {
@@ -179,8 +220,8 @@ __device__ __forceinline__ void ct_prefetch(int tid, const S& src, float2 (&v)[F
 #pragma unroll
   for (int i = 0; i < MAXB; ++i) {
     const int it = tid + i * T;
-    const int line = LF ? it % NL : it / NB;
-    const int j = LF ? it / NL : it % NB;
+    int line, j;
+    item_of<NL, NB, MAXB * T, LF>(it, line, j);
     if ((TOTAL % T == 0) || it < TOTAL) {
 #pragma unroll
       for (int r = 0; r < R; ++r) v[i][r] = src.ld(line, j + r * NB);
@@ -204,8 +245,8 @@ __device__ __forceinline__ void ct_stage(int tid_in, const float2* tw, const S& 
 #pragma unroll
   for (int i = 0; i < MAXB; ++i) {
     const int it = tid + i * T;
-    const int line = LF ? it % NL : it / NB;
-    const int j = LF ? it / NL : it % NB;
+    int line, j;
+    item_of<NL, NB, MAXB * T, LF>(it, line, j);
     ln[i] = line;
     jb[i] = j;
     if (FULL || it < TOTAL) {
@@ -224,17 +265,17 @@ __device__ __forceinline__ void ct_stage(int tid_in, const float2* tw, const S& 
     const int it = tid + i * T;
     if (FULL || it < TOTAL) {
       const int j = jb[i];
-      const int k = j % NS;
+      const int k = DivC<NS, NB>::mod(j);
       if (NS > 1) {
 #pragma unroll
         for (int r = 1; r < R; ++r) {
-          float2 w = tw[k * r * TWS];
+          float2 w = tw[__umul24((unsigned)k, r * TWS)];
           if (INV) w.y = -w.y;
           v[i][r] = cmul(v[i][r], w);
         }
       }
       Dft<R, INV>::run(v[i]);
-      const int base = (j - k) * R + k;
+      const int base = (int)__umul24((unsigned)(j - k), R) + k;
 #pragma unroll
       for (int r = 0; r < R; ++r) dst.st(ln[i], base + r * NS, v[i][r], i, r);
     }
@@ -290,8 +331,7 @@ struct LastMap {
   static constexpr int MAXB = (TOTAL + T - 1) / T;
   static __device__ __forceinline__ bool at(int tid, int i, int& line, int& j) {
     const int it = tid + i * T;
-    line = LF ? it % NL : it / NB;
-    j = LF ? it / NL : it % NB;
+    item_of<NL, NB, MAXB * T, LF>(it, line, j);
     return (TOTAL % T == 0) || it < TOTAL;
   }
 };

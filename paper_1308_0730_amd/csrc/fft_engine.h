@@ -142,8 +142,10 @@ template <int PITCH>
 struct LdsRow {
   float2* p;
   static constexpr bool lds = true;
-  __device__ __forceinline__ float2 ld(int line, int pos) const { return p[line * PITCH + pos]; }
-  __device__ __forceinline__ void st(int line, int pos, float2 v) const { p[line * PITCH + pos] = v; }
+  __device__ __forceinline__ float2 ld(int line, int pos) const { return p[__umul24((unsigned)line, PITCH) + pos]; }
+  __device__ __forceinline__ void st(int line, int pos, float2 v) const {
+    p[__umul24((unsigned)line, PITCH) + pos] = v;
+  }
 };
 
 // Global tile: element (line, pos) at base[line * ls + pos * ps] (32-bit

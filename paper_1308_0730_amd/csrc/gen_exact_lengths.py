@@ -143,6 +143,48 @@ def col_classes():
     return out
 
 
+# Two-pass x kernels (half-rows up to TP_MAX_ROW): radices up to 16 and rows
+# per wave by a cost model, vector operations of the butterflies plus LDS
+# round trips, so that the butterfly counts of every stage nearly fill whole
+# waves: 72 points as 9 x 8 with 7 rows per wave keep 56 and 63 of 64 lanes
+# busy, where 8 x 3 x 3 with 8 rows leaves the radix-8 stage at 72 butterflies
+# (two rounds, the second of 8 lanes).
+TP_MAX_ROW = 256
+DFT_OPS = {2: 4, 3: 14, 4: 16, 5: 36, 6: 46, 8: 56, 9: 100, 10: 108, 12: 122, 15: 210, 16: 170}
+
+
+def tp_row_plan(M):
+    best = None
+
+    def seqs(n, cur):
+        if n == 1:
+            yield cur
+            return
+        if len(cur) >= 5:
+            return
+        for r in DFT_OPS:
+            if n % r == 0:
+                yield from seqs(n // r, cur + [r])
+
+    for seq in seqs(M, []):
+        for rpw in range(1, 17):
+            if -(-M * rpw // 64) > 10:
+                break
+            cost = 0
+            regs = 0
+            for i, r in enumerate(seq):
+                slots = -(-(M // r) * rpw // 64)
+                regs = max(regs, slots * r)
+                cost += slots * (DFT_OPS[r] + (4 * (r - 1) if i else 0) + 3 * r + 8)
+            if regs > 16:
+                continue
+            # per row; fewer rows per wave (more waves) on a near tie
+            key = (round(cost / rpw * (1 + 0.004 * rpw), 3), len(seq))
+            if best is None or key < best[0]:
+                best = (key, rpw, seq)
+    return best[1], best[2]
+
+
 def main():
     lines = ["// Generated by gen_exact_lengths.py: lengths with compile-time transform",
              "// plans for every 5-smooth size.  Do not edit by hand.",
@@ -160,6 +202,13 @@ def main():
         rad = row_radices(M)
         rpw = row_rows(M)
         lines.append(f"  X({M}, 4, {rpw}, {', '.join(map(str, rad))}){end}")
+    lines.append("")
+    lines += ["", "// X(M, rows per wave, radices...) of the two-pass x kernels", "#define MVD_TP_ROW(X) \\"]
+    tps = [M for M in rows if M <= TP_MAX_ROW]
+    for i, M in enumerate(tps):
+        end = " \\" if i + 1 < len(tps) else ""
+        rpw, rad = tp_row_plan(M)
+        lines.append(f"  X({M}, {rpw}, {', '.join(map(str, rad))}){end}")
     lines.append("")
     # column length classes: the per-length plans of one thread count and
     # length range, for kernels that serve blocks of several lengths

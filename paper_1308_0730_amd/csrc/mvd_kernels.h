@@ -91,6 +91,25 @@ hipError_t mvd_launch_x_exact_win(const LaunchArgs& a, int M, int mode, int v, P
 hipError_t mvd_launch_zext_exact(const LaunchArgs& a, int L, int v, int role, int conjH, float2* s_out,
                                  const float2* s_in, double2* acc, int acc_mode);
 
+// Two-pass convolutions (mvd_two_pass.h).
+struct TpArgs {
+  const TpJob* jobs;  // device table
+  int njobs;
+  const float2* tw;
+  hipStream_t stream;
+  int grid;
+};
+int mvd_tp_row(int M, int* rows, size_t* lds_row);  // rows per wave, LDS bytes per row; 0 if none
+hipError_t mvd_launch_x_tp(const TpArgs& a, int M, int waves, size_t lds, int mode, int v, Partial* parts, int* flags,
+                           int opt);
+hipError_t mvd_launch_x_tp_update(const TpArgs& a, int M, int waves, size_t lds, int v, Partial* parts, int* flags,
+                                  int opt);
+hipError_t mvd_launch_x_tp_comb(const TpArgs& a, int M, int waves, size_t lds, int mode, int v, Partial* parts,
+                                int* flags, int opt);
+hipError_t mvd_launch_plane(const TpArgs& a, int threads, size_t lds, int v, int role, int conj, int src_saved);
+// kernel spectra of every view of a.jobs[0] (grid: its planes times its views)
+hipError_t mvd_launch_plane_kernel(const TpArgs& a, size_t lds, int role, float* out);
+
 // weight normalisation (mvd_weights.hip), on one block's [nviews][V] weights
 hipError_t mvd_launch_overlap_stats(const float* w, int nviews, int64_t V, unsigned* cmin,
                                     unsigned long long* csum, unsigned long long* ncov, hipStream_t s);

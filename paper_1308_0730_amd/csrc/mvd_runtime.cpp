@@ -71,6 +71,10 @@ struct Block {
   std::vector<std::array<int, 3>> psf_dims;  // raw extents {kx, ky, kz}
   double s = 0;
   float eps = 0, lamp = 0;
+  // two-pass convolutions: the split of ny (0: the block has no two-pass
+  // form) and the kernel spectra, built on first use
+  int tpR = 0;
+  float* K2[N_ROLES] = {nullptr, nullptr, nullptr, nullptr};
 };
 
 }  // namespace
@@ -137,8 +141,34 @@ struct mvd_handle {
   // sorted job order (the block-major schedules), set with the per-length
   // plans of all three kinds
   std::vector<Group> bgroups[3];
+  // two-pass convolutions (mvd_two_pass.h): planned at create, used until
+  // launch shapes are set; one launch covers every block of a pass where the
+  // blocks have equal extents, else one block (on its lane; combined updates
+  // only: the sequential runs of uneven blocks let the lanes run apart for a
+  // whole iteration instead)
+  struct TpPass {
+    int grid = 0;     // tiles of the block
+    int threads = 0;
+    size_t lds = 0;
+    int off = 0;      // x tiles of the blocks before it
+  };
+  bool tp_planned = false;
+  bool tiles_chosen = false;  // launch shapes were set (mvd_set_tiles): four-pass
+  TpJob* d_tp = nullptr;                  // allocated, with the rest, on first use (ensure_two_pass)
+  Partial* d_tp_parts = nullptr;
+  std::vector<void*> tp_allocs;           // memory of the two-pass form: given back when another
+  bool tp_allocating = false;             // allocation fails (tp_release)
+  int64_t role_runs[N_ROLES] = {0, 0, 0, 0};  // iterations asked for per kernel role
+  std::vector<TpJob> tpjobs;              // one per block
+  std::vector<TpPass> tp_x, tp_p;         // per block: the x and the plane pass
+  bool tp_even = false;                   // equal extents
+  int tp_tiles = 0;                       // x tiles of all blocks
+  bool k2_built[N_ROLES] = {false, false, false, false};
+  int stat_grid = 0;                      // the last run's partial results: x tiles
+  Partial* stat_parts = nullptr;          // and place
   // MVD_SCHEDULE_*: the order in which a multi-block handle's lanes take the
-  // passes of a run, and the graphs of whole runs (key: variant, n)
+  // passes of a run, and the graphs of whole runs (key: variant, + 4 in the
+  // two-pass form, and n)
   int schedule = 0;
   std::map<std::pair<int, int>, hipGraphExec_t> run_exec;
   FftPlan* d_plans = nullptr;
@@ -158,13 +188,15 @@ struct mvd_handle {
   int max_len[3] = {0, 0, 0};
   int uniform_len[3] = {0, 0, 0};  // the common length of a pass kind, 0 if the blocks differ
   size_t parts_cap = 0;
-  bool spec_valid = false;
+  bool spec_valid = false;  // spec holds psi's x-stage spectrum ...
+  bool spec_tp = false;     // ... in the two-pass layout
   bool linear = false;            // MVD_BOUNDARY_LINEAR
   bool built[N_ROLES] = {true, false, false, false};
   int64_t iterations = 0;
-  // one graph per (scheme, variant): scheme 0 sequential, 1 combined with
-  // the geometric mean, 2 combined with the arithmetic mean
-  hipGraphExec_t exec[3 * 4] = {};
+  // one graph per (form, scheme, variant): four or two passes; scheme 0
+  // sequential, 1 combined with the geometric mean, 2 combined with the
+  // arithmetic mean
+  hipGraphExec_t exec[2 * 3 * 4] = {};
   // differentiated form: runtime-plan shapes, grids and buffers (block 0)
   int rt_cfg[3] = {-1, -1, -1};
   int rt_grid[3] = {0, 0, 0};
@@ -201,20 +233,33 @@ struct mvd_handle {
   int64_t w_stage_cap = 0;
   std::string err;
 
+  void* raw_alloc(size_t bytes) {
+    if (alloc) return alloc(bytes, actx);
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+  }
+
+  void raw_free(void* p) {
+    if (alloc && free_fn)
+      free_fn(p, actx);
+    else if (!alloc)
+      (void)hipFree(p);
+  }
+
+  // Give back the two-pass form's memory (the four passes need none of it);
+  // false if there is none.
+  bool tp_release();
+
   void* dalloc(size_t bytes) {
     bytes = (bytes + 255) & ~size_t(255);
-    void* p = nullptr;
-    if (alloc) {
-      p = alloc(bytes, actx);
-      if (!p) throw Error(MVD_ENOMEM, "allocator callback failed for " + std::to_string(bytes) + " bytes");
-    } else {
-      hipError_t e = hipMalloc(&p, bytes);
-      if (e != hipSuccess || !p) {
-        (void)hipGetLastError();
-        throw Error(MVD_ENOMEM, "hipMalloc failed for " + std::to_string(bytes) + " bytes");
-      }
-    }
-    allocs.push_back(p);
+    void* p = raw_alloc(bytes);
+    if (!p && !tp_allocating && tp_release()) p = raw_alloc(bytes);
+    if (!p)
+      throw Error(MVD_ENOMEM, std::string(alloc ? "allocator callback" : "hipMalloc") + " failed for " +
+                                  std::to_string(bytes) + " bytes");
+    (tp_allocating ? tp_allocs : allocs).push_back(p);
     return p;
   }
 
@@ -227,12 +272,9 @@ struct mvd_handle {
     for (auto& kv : run_exec) (void)hipGraphExecDestroy(kv.second);
     run_exec.clear();
     if (cap) (void)hipDeviceSynchronize();
-    for (void* p : allocs) {
-      if (alloc && free_fn)
-        free_fn(p, actx);
-      else if (!alloc)
-        (void)hipFree(p);
-    }
+    for (void* p : tp_allocs) raw_free(p);
+    tp_allocs.clear();
+    for (void* p : allocs) raw_free(p);
     allocs.clear();
     if (cap) (void)hipStreamDestroy(cap);
     cap = nullptr;
@@ -418,6 +460,8 @@ int total_tiles(const mvd_handle* h, int kind, int param) {
   return (int)t;
 }
 
+void tp_upload(mvd_handle* h);
+
 // Transform length of a pass kind in a block: x the half-row nx/2, y ny, z nz.
 int job_len(const Block& B, int kind) { return kind == PASS_X ? B.M : kind == PASS_Y ? B.ny : B.nz; }
 
@@ -499,6 +543,7 @@ void build_jobs(mvd_handle* h) {
                             h->stream));
   }
   HIPCHECK(hipStreamSynchronize(h->stream));
+  tp_upload(h);
 }
 
 // Drop every cached graph (launch shapes, kernel spectra or the schedule
@@ -515,6 +560,27 @@ void drop_graphs(mvd_handle* h) {
   for (auto& kv : h->run_exec) (void)hipGraphExecDestroy(kv.second);
   h->run_exec.clear();
 }
+
+}  // namespace
+
+bool mvd_handle::tp_release() {
+  if (tp_allocs.empty()) return false;
+  drop_graphs(this);
+  HIPCHECK(hipStreamSynchronize(stream));
+  for (void* p : tp_allocs) raw_free(p);
+  tp_allocs.clear();
+  for (auto& B : blocks)
+    for (float*& k : B.K2) k = nullptr;
+  for (bool& b : k2_built) b = false;
+  d_tp = nullptr;
+  d_tp_parts = nullptr;
+  tp_planned = false;
+  if (spec_tp) spec_valid = false;
+  spec_tp = false;
+  return true;
+}
+
+namespace {
 
 // Select the launch shapes of the three pass kinds; recomputes the grids,
 // grows the partials buffer and drops the cached graphs.
@@ -690,8 +756,96 @@ void alloc_block(mvd_handle* h, Block& B, bool weights) {
   if (weights) B.w = (float*)h->dalloc((size_t)N * B.V * sizeof(float));
 }
 
+// ---- two-pass convolutions ---------------------------------------------------
+
+constexpr int kTpSplits[] = {1, 2, 3, 4, 5, 6, 8, 9};
+
+size_t tp_plane_lds(int n1, int nz) { return ((size_t)nz * (n1 | 1) + nz + n1) * sizeof(float2); }
+
+// Split R of ny = R n1 for the two-pass form of a block, 0 if it has none.
+// A function of the block's own extents, so that a block gives the same
+// bits alone and in a batch.
+//
+// Up to 5 Mi spectrum values the form is the faster one (three views, four
+// iterations, weights; four-pass against two-pass: 64^3 615 / 503 us, 128^3
+// 1119 / 831, 150x108x90 1104 / 771, 256x256x128 2210 / 2116, 240x400x100
+// 2723 / 2420); above, the planes need so large a split that an x tile
+// writes short pieces of lines (512x256x128 3556 / 4627 us), and the column
+// passes run at the copy rate anyway.
+//
+// Planes are kept within 64 KB.  Small volumes are latency: they take the
+// largest split, which leaves the plane pass the fewest stages and the most
+// workgroups (128^3, four views: R = 2 136 us per two view-updates, 4 133,
+// 8 117).  The others take the smallest split whose plane is at most 32 KB
+// (five workgroups per CU), for the longest contiguous pieces per x tile.
+int tp_split(const Block& B) {
+  int rows;
+  size_t lds_row;
+  const int64_t n = (int64_t)(B.M + 1) * B.ny * B.nz;
+  if (!mvd_tp_row(B.M, &rows, &lds_row) || n > (int64_t)5 << 20) return 0;
+  const bool small = n <= (int64_t)3 << 19;
+  int best = 0;
+  size_t best_lds = 0;
+  for (int R : kTpSplits) {
+    const int n1 = B.ny / R;
+    if (B.ny % R || n1 < 4) continue;
+    const size_t lds = tp_plane_lds(n1, B.nz);
+    if (lds > (size_t)64 << 10) continue;
+    // at least four y1 values per x tile of eight waves: shorter pieces of
+    // lines cost the x passes more than the plane pass gives
+    if (TP_MAX_WAVES * rows / R < 4) continue;
+    if (small) {
+      if (best && n1 < 8) continue;
+      best = R;
+    } else if (!best || best_lds > (size_t)32 << 10) {
+      best = R, best_lds = lds;
+    }
+  }
+  return best;
+}
+
+// Radices of an in-place plane transform: the fewest stages, then the
+// smallest largest radix.
+std::vector<int> tp_radices(int L) {
+  static const int rs[] = {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
+  std::vector<int> best;
+  std::vector<int> cur;
+  auto rec = [&](auto&& self, int n, int top) -> void {
+    if (n == 1) {
+      if (best.empty() || cur.size() < best.size() ||
+          (cur.size() == best.size() && cur[0] < best[0]))
+        best = cur;
+      return;
+    }
+    if (!best.empty() && cur.size() >= best.size()) return;
+    for (int r : rs)
+      if (r <= top && n % r == 0) {
+        cur.push_back(r);
+        self(self, n / r, r);
+        cur.pop_back();
+      }
+  };
+  rec(rec, L, 16);
+  return best;
+}
+
+int tp_stages(int L, TpStage* st) {
+  const auto r = tp_radices(L);
+  if (r.empty() || r.size() > TP_MAX_STAGES) bad("no in-place plan for length " + std::to_string(L));
+  int done = 1;
+  for (size_t i = 0; i < r.size(); ++i) {
+    st[i].radix = r[i];
+    st[i].nb = L / (done * r[i]);
+    st[i].tws = done;
+    st[i].mg_nb = mvd_magic((unsigned)st[i].nb);
+    done *= r[i];
+  }
+  return (int)r.size();
+}
+
 // FFT plans and twiddle tables of a block's lengths.
-void add_plans(mvd_handle* h, const Block& B, std::vector<FftPlan>& plans, std::vector<float2>& tw) {
+void add_plans(mvd_handle* h, Block& B, std::vector<FftPlan>& plans, std::vector<float2>& tw) {
+  if (!h->blocked && h->force_cfg == 0) B.tpR = tp_split(B);
   plan_for(h, B.M, plans, tw);
   plan_for(h, B.ny, plans, tw);
   plan_for(h, B.nz, plans, tw);
@@ -700,6 +854,92 @@ void add_plans(mvd_handle* h, const Block& B, std::vector<FftPlan>& plans, std::
     const auto t = mvdh::twiddles(B.nx);
     for (int k = 0; k < B.M; ++k) tw.push_back(make_float2((float)t[k].real(), (float)t[k].imag()));
   }
+}
+
+// Job and launches of a block's two-pass form (false: it has none); plans:
+// the host plan list, for the twiddle offsets; blocks: how many share a launch.
+bool tp_plan_block(mvd_handle* h, const Block& B, const std::vector<FftPlan>& plans, int blocks, TpJob& j,
+                   mvd_handle::TpPass& x, mvd_handle::TpPass& p) {
+  if (!B.tpR) return false;
+  j.nx = B.nx, j.ny = B.ny, j.nz = B.nz, j.M = B.M;
+  j.nviews = h->nviews;
+  j.R = B.tpR;
+  j.n1 = B.ny / j.R;
+  j.pl = j.n1 | 1;
+  auto tw = [&](int len) { return plans[h->plan_of_len.at(len)].tw; };
+  j.tw_x = tw(B.M), j.tw_y = tw(B.ny), j.tw_z = tw(B.nz);
+  j.pp = h->pp_of_nx.at(B.nx);
+  j.nsz = tp_stages(B.nz, j.sz);
+  j.nsy = tp_stages(j.n1, j.sy);
+  j.yz_tiles = (B.M + 1) * j.R;
+  j.V = B.V;
+  j.k2_elems = (int64_t)(B.M + 1) * B.ny * B.nz;
+  // x tiles.  Waves per workgroup: row slots transformed, plus the rows
+  // weighted for short pieces of lines (2 / a); eight waves only where the
+  // tiles are few (their barriers cost more than the longer pieces give:
+  // 8 x 144x120x96 5.09 ms with eight, 4.47 with four; 128^3 2.34 against
+  // 2.39) or four leave very short pieces.
+  int rows, w = 0;
+  size_t lds_row;
+  mvd_tp_row(B.M, &rows, &lds_row);
+  auto lds_of = [&](int wv) { return (size_t)wv * rows * (lds_row + sizeof(float2)) + (size_t)2 * B.M * sizeof(float2); };
+  double best = 0;
+  for (int wv = 1; wv <= TP_MAX_WAVES; wv *= 2) {
+    const int most = std::min({wv * rows / j.R, j.n1, 32});
+    if (most < 1 || lds_of(wv) > (size_t)64 << 10) continue;
+    const int at = mvd_cdiv(j.n1, most), a = mvd_cdiv(j.n1, at);  // near-equal tiles of a z plane
+    double cost = (double)at * wv * rows + (double)j.ny * (1 + 2.0 / a);
+    if (wv == 8 && (int64_t)blocks * j.nz * at > 400) cost *= 1.15;
+    if (!w || cost < best) w = wv, best = cost, j.a = a;
+  }
+  if (!w) return false;
+  j.atiles = mvd_cdiv(j.n1, j.a);
+  const int np = j.M / 2 + 1;
+  j.ks = j.a;
+  while (j.ks > 1 && mvd_cdiv(np, j.ks) * j.ks * 8 > 9 * np) j.ks = (j.ks + 1) / 2;
+  j.kg = mvd_cdiv(np, j.ks);
+  j.mg_n1 = mvd_magic(j.n1), j.mg_nz = mvd_magic(B.nz);
+  j.mg_a = mvd_magic(j.a), j.mg_kg = mvd_magic(j.kg), j.mg_R = mvd_magic(j.R);
+  x = {j.nz * j.atiles, 64 * w, lds_of(w), 0};
+  // plane pass: whole SIMDs, two waves for planes too small to feed four
+  p = {j.yz_tiles, j.n1 * j.nz >= 1536 ? 256 : 128, tp_plane_lds(j.n1, j.nz), 0};
+  return true;
+}
+
+void tp_plan(mvd_handle* h, const std::vector<FftPlan>& plans) {
+  const int nb = (int)h->blocks.size();
+  const Block& B = h->blocks[0];
+  h->tp_even = true;
+  for (const auto& X : h->blocks) h->tp_even &= X.nx == B.nx && X.ny == B.ny && X.nz == B.nz;
+  h->tpjobs.assign(nb, TpJob{});
+  h->tp_x.resize(nb), h->tp_p.resize(nb);
+  int64_t xt = 0, pt = 0;
+  for (int b = 0; b < nb; ++b) {
+    if (!tp_plan_block(h, h->blocks[b], plans, h->tp_even ? nb : 1, h->tpjobs[b], h->tp_x[b], h->tp_p[b])) return;
+    h->tp_x[b].off = (int)xt;
+    xt += h->tp_x[b].grid;
+    pt += (int64_t)h->tp_p[b].grid * h->nviews;
+    if (xt > 0x7fffffff || pt > 0x7fffffff) return;
+  }
+  h->tp_tiles = (int)xt;
+  h->tp_planned = true;
+}
+
+// Refresh the pointers of the two-pass jobs (buffers come and go).
+void tp_upload(mvd_handle* h) {
+  if (!h->d_tp) return;
+  for (size_t i = 0; i < h->tpjobs.size(); ++i) {
+    TpJob& j = h->tpjobs[i];
+    const Block& B = h->blocks[i];
+    j.psi = B.psi, j.spec = B.spec, j.phi = B.phi, j.w = B.w, j.acc = B.acc, j.saved = B.saved;
+    for (int r = 0; r < N_ROLES; ++r) j.K2[r] = B.K2[r], j.H[r] = B.H[r];
+    j.eps = B.eps, j.lamp = B.lamp;
+    j.h_main = B.h_main, j.h_elems = B.h_elems;
+    j.Mp = B.Mp, j.kz = B.kz, j.cz = B.cz;
+  }
+  HIPCHECK(hipMemcpyAsync(h->d_tp, h->tpjobs.data(), h->tpjobs.size() * sizeof(TpJob), hipMemcpyHostToDevice,
+                          h->stream));
+  HIPCHECK(hipStreamSynchronize(h->stream));
 }
 
 // The rest of a create once every block holds its inputs and kernel planes:
@@ -733,6 +973,7 @@ void finish_create(mvd_handle* h, std::vector<FftPlan>& plans, std::vector<float
     if (B.nz != maxZ) h->uniform_len[PASS_Z] = 0;
   }
   set_tiles(h, pick_cfg(h, PASS_X), pick_cfg(h, PASS_Y), pick_cfg(h, PASS_Z));
+  tp_plan(h, plans);
   h->d_flags = (int*)h->dalloc(sizeof(int));
   h->d_flux = (double*)h->dalloc(N * sizeof(double));
   h->d_ratio = (unsigned long long*)h->dalloc(N * sizeof(unsigned long long));
@@ -1157,6 +1398,94 @@ void run_z(mvd_handle* h, hipStream_t s, int v, int role, int conjH, int src_sav
   });
 }
 
+// Memory and kernel spectra of the two-pass form for a role (from its kernel
+// planes).  False, and the form given up, when the memory is not there.
+bool ensure_two_pass(mvd_handle* h, int role) {
+  if (h->k2_built[role]) return true;
+  const size_t nb = h->blocks.size();
+  h->tp_allocating = true;
+  bool ok = true;
+  try {
+    if (!h->d_tp) {
+      h->d_tp_parts = (Partial*)h->dalloc((size_t)h->nviews * h->tp_tiles * sizeof(Partial));
+      h->d_tp = (TpJob*)h->dalloc(h->tpjobs.size() * sizeof(TpJob));
+    }
+    for (auto& B : h->blocks)
+      if (!B.K2[role])
+        B.K2[role] = (float*)h->dalloc((size_t)h->nviews * (B.M + 1) * B.ny * B.nz * sizeof(float2));
+  } catch (const Error&) {
+    ok = false;
+  }
+  h->tp_allocating = false;
+  if (!ok) {
+    (void)h->tp_release();
+    h->tp_planned = false;
+    return false;
+  }
+  tp_upload(h);
+  for (size_t b = 0; b < nb; ++b) {
+    const TpArgs a{h->d_tp + b, 1, h->d_tw, h->stream, h->tp_p[b].grid * h->nviews};
+    HIPCHECK(mvd_launch_plane_kernel(a, h->tp_p[b].lds, role, h->blocks[b].K2[role]));
+  }
+  h->k2_built[role] = true;
+  return true;
+}
+
+// Whether a run of n iterations of this role takes the two-pass form.  Its
+// spectra are built once a handle has been asked for a second iteration of a
+// role: for a single one the four passes are done first.
+bool use_two_pass(mvd_handle* h, int role, int n, bool combined) {
+  if (!h->tp_planned || h->tiles_chosen || !(h->tp_even || combined)) return false;
+  const bool again = (h->role_runs[role] += n) >= 2;
+  if (!again && !h->k2_built[role]) return false;
+  return ensure_two_pass(h, ROLE_P) && ensure_two_pass(h, role);
+}
+
+// One launch of a pass of the two-pass form: blocks [b0, b0 + n), n > 1 only
+// where they have equal extents.
+void tp_launch_x(mvd_handle* h, hipStream_t s, int b0, int n, int mode, int v, int opt) {
+  const auto& x = h->tp_x[b0];
+  const TpArgs a{h->d_tp + b0, n, h->d_tw, s, n * x.grid};
+  Partial* parts = h->d_tp_parts + (size_t)v * h->tp_tiles + x.off;
+  HIPCHECK(mvd_launch_x_tp(a, h->tpjobs[b0].M, x.threads / 64, x.lds, mode, v, mode ? parts : nullptr, h->d_flags,
+                           opt));
+}
+void tp_launch_plane(mvd_handle* h, hipStream_t s, int b0, int n, int v, int role, int conj, int src_saved) {
+  const auto& p = h->tp_p[b0];
+  const TpArgs a{h->d_tp + b0, n, h->d_tw, s, n * p.grid};
+  HIPCHECK(mvd_launch_plane(a, p.threads, p.lds, v, role, conj, src_saved));
+}
+// A pass over every block: f(stream, first block, blocks), forked over the
+// lanes and joined for uneven blocks (see run_groups).
+template <class F>
+void tp_all(mvd_handle* h, hipStream_t s, F&& f) {
+  const int nb = (int)h->blocks.size();
+  if (h->tp_even) {
+    f(s, 0, nb);
+    return;
+  }
+  HIPCHECK(hipEventRecord(h->ev_fork, s));
+  for (int l = 0; l < h->nside; ++l) HIPCHECK(hipStreamWaitEvent(h->side[l], h->ev_fork, 0));
+  for (int b = 0; b < nb; ++b) f(h->block_lane[b] ? h->side[h->block_lane[b] - 1] : s, b, 1);
+  for (int l = 0; l < h->nside; ++l) {
+    HIPCHECK(hipEventRecord(h->ev_join[l], h->side[l]));
+    HIPCHECK(hipStreamWaitEvent(s, h->ev_join[l], 0));
+  }
+}
+void tp_x(mvd_handle* h, hipStream_t s, int mode, int v, int opt) {
+  tp_all(h, s, [&](hipStream_t st, int b0, int n) { tp_launch_x(h, st, b0, n, mode, v, opt); });
+}
+void tp_plane(mvd_handle* h, hipStream_t s, int v, int role, int conj, int src_saved) {
+  tp_all(h, s, [&](hipStream_t st, int b0, int n) { tp_launch_plane(h, st, b0, n, v, role, conj, src_saved); });
+}
+// A view-update of blocks of equal extents.
+void tp_view(mvd_handle* h, hipStream_t s, int b0, int n, int v, int role, int conj_back) {
+  tp_launch_plane(h, s, b0, n, v, ROLE_P, 0, 0);
+  tp_launch_x(h, s, b0, n, 1, v, XOPT_SPEC);
+  tp_launch_plane(h, s, b0, n, v, role, conj_back, 0);
+  tp_launch_x(h, s, b0, n, 2, v, XOPT_SPEC);
+}
+
 // Per-launch event timing of the passes (profiling hook): kinds are
 // 0 y forward, 1 y inverse, 2 z product, 3 x ratio, 4 x update.
 struct PassTimer {
@@ -1184,6 +1513,10 @@ struct PassTimer {
 void enqueue_view_passes(mvd_handle* h, hipStream_t s, int variant, int v, PassTimer* t, bool spec_out) {
   const int role = variant == MVD_RL ? ROLE_P : variant;
   const int conj_back = variant == MVD_RL ? 1 : 0;
+  if (h->spec_tp && !t) {
+    tp_view(h, s, 0, (int)h->blocks.size(), v, role, conj_back);
+    return;
+  }
   Partial* parts = h->d_parts + (size_t)v * h->grid_x;
   auto timed = [&](int kind, auto&& fn) {
     if (t) t->mark(kind);
@@ -1252,6 +1585,10 @@ void enqueue_iteration(mvd_handle* h, hipStream_t s, int variant, PassTimer* t =
 void enqueue_view_block(mvd_handle* h, hipStream_t s, int variant, int v, int b) {
   const int role = variant == MVD_RL ? ROLE_P : variant;
   const int conj_back = variant == MVD_RL ? 1 : 0;
+  if (h->spec_tp) {
+    tp_view(h, s, b, 1, v, role, conj_back);
+    return;
+  }
   Partial* parts = h->d_parts + (size_t)v * h->grid_x;
   const auto& gx = h->bgroups[PASS_X][b];
   const auto& gy = h->bgroups[PASS_Y][b];
@@ -1276,6 +1613,7 @@ void enqueue_view_block(mvd_handle* h, hipStream_t s, int variant, int v, int b)
 
 bool block_major(const mvd_handle* h) {
   if (h->schedule == MVD_SCHEDULE_PASS_MAJOR || h->blocks.size() < 2 || h->blocked || h->no_alloc) return false;
+  if (h->spec_tp) return true;
   for (int k = 0; k < 3; ++k)
     if (h->bgroups[k].size() != h->blocks.size()) return false;
   return true;
@@ -1322,6 +1660,20 @@ void enqueue_combined_iteration(mvd_handle* h, hipStream_t s, int variant, bool 
   const int role = variant == MVD_RL ? ROLE_P : variant;
   const int conj_back = variant == MVD_RL ? 1 : 0;
   const int N = h->nviews;
+  if (h->spec_tp) {
+    // the saved spectrum is the x passes': every view's plane pass reads it
+    for (const auto& B : h->blocks)
+      HIPCHECK(hipMemcpyAsync(B.saved, B.spec, (size_t)(B.M + 1) * B.ny * B.nz * sizeof(float2),
+                              hipMemcpyDeviceToDevice, s));
+    for (int v = 0; v < N; ++v) {
+      const int opt = (v == 0 ? XOPT_FIRST : 0) | (geo ? XOPT_GEO : 0);
+      tp_plane(h, s, v, ROLE_P, 0, 1);
+      tp_x(h, s, 1, v, XOPT_SPEC);
+      tp_plane(h, s, v, role, conj_back, 0);
+      tp_x(h, s, v < N - 1 ? 3 : 4, v, opt | XOPT_SPEC);
+    }
+    return;
+  }
   run_y(h, s, 0, 0);
   for (const auto& B : h->blocks)
     HIPCHECK(hipMemcpyAsync(B.saved, B.spec, B.spec_elems * 2 * sizeof(float), hipMemcpyDeviceToDevice, s));
@@ -1357,19 +1709,40 @@ void ensure_combined(mvd_handle* h) {
   if (grown) build_jobs(h);
 }
 
-void prepare_run(mvd_handle* h, int variant) {
+// n: iterations asked for; classic: the launches that the profiler times,
+// never the two-pass form; combined: combined updates follow.
+void prepare_run(mvd_handle* h, int variant, int n, bool classic = false, bool combined = false) {
   if (variant < MVD_RL || variant > MVD_OPT2) bad("variant must be MVD_RL, MVD_EFF, MVD_OPT1 or MVD_OPT2");
   const int role = variant == MVD_RL ? ROLE_P : variant;
   ensure_role(h, role);
-  if (!h->spec_valid && !h->blocked) {
-    run_x(h, h->stream, 0, 0, nullptr, XOPT_SPEC);
+  const bool two = !classic && use_two_pass(h, role, n, combined);
+  h->stat_grid = two ? h->tp_tiles : h->grid_x;
+  h->stat_parts = two ? h->d_tp_parts : h->d_parts;
+  if ((!h->spec_valid || h->spec_tp != two) && !h->blocked) {
+    if (two)
+      tp_x(h, h->stream, 0, 0, XOPT_SPEC);
+    else
+      run_x(h, h->stream, 0, 0, nullptr, XOPT_SPEC);
     h->spec_valid = true;
   }
+  h->spec_tp = two;
+}
+
+// Whether runs replay graphs: only where every block sits on one lane, so
+// that the graph is a chain.  A graph whose branches are the lanes of
+// uneven blocks has ended the process inside its replay (a host segmentation
+// fault, now and then, at hundreds of replays); those runs launch directly,
+// which keeps ahead of the device too.
+bool replay(const mvd_handle* h) {
+  if (!h->use_graphs) return false;
+  for (int l : h->block_lane)
+    if (l) return false;
+  return true;
 }
 
 // scheme 0: sequential; 1, 2: combined with the geometric / arithmetic mean
 hipGraphExec_t graph_for(mvd_handle* h, int variant, int scheme = 0) {
-  hipGraphExec_t& slot = h->exec[scheme * 4 + variant];
+  hipGraphExec_t& slot = h->exec[(h->spec_tp ? 12 : 0) + scheme * 4 + variant];
   if (slot) return slot;
   hipGraph_t g = nullptr;
   HIPCHECK(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
@@ -1395,12 +1768,12 @@ hipGraphExec_t graph_for(mvd_handle* h, int variant, int scheme = 0) {
 // Statistics of the last iteration from the partial results (the block-wise
 // form's update passes count and sum the own voxels of every block).
 void reduce_stats(mvd_handle* h, hipStream_t s) {
-  HIPCHECK(mvd_launch_reduce(h->d_parts, h->grid_x, h->nviews, h->d_flux, h->d_ratio, h->d_neg, s));
+  HIPCHECK(mvd_launch_reduce(h->stat_parts, h->stat_grid, h->nviews, h->d_flux, h->d_ratio, h->d_neg, s));
 }
 
 // The graph of a whole block-major run of n iterations (one launch per run).
 hipGraphExec_t run_graph_for(mvd_handle* h, int variant, int n) {
-  const auto key = std::make_pair(variant, n);
+  const auto key = std::make_pair(variant + (h->spec_tp ? 4 : 0), n);
   auto it = h->run_exec.find(key);
   if (it != h->run_exec.end()) return it->second;
   hipGraph_t g = nullptr;
@@ -1433,13 +1806,13 @@ void iterate_impl(mvd_handle* h, int n, int variant) {
   if (n < 0) bad("n must be >= 0");
   if (n == 0) return;
   h->rec_token = 0;
-  prepare_run(h, variant);
+  prepare_run(h, variant, n);
   if (block_major(h)) {
-    if (h->use_graphs)
+    if (replay(h))
       HIPCHECK(hipGraphLaunch(run_graph_for(h, variant, n), h->stream));
     else
       enqueue_run_blocks(h, h->stream, variant, n);
-  } else if (h->use_graphs) {
+  } else if (replay(h)) {
     hipGraphExec_t ex = graph_for(h, variant);
     for (int i = 0; i < n; ++i) HIPCHECK(hipGraphLaunch(ex, h->stream));
   } else {
@@ -1459,16 +1832,16 @@ void iterate_combined_impl(mvd_handle* h, int n, int variant, int mean) {
   for (const auto& B : h->blocks)
     if (B.w) bad("combined updates take no weights (weights apply to sequential view-updates)");
   if (n == 0) return;
-  prepare_run(h, variant);
   ensure_combined(h);
+  prepare_run(h, variant, n, false, true);
   const bool geo = mean == MVD_MEAN_GEOMETRIC;
-  if (h->use_graphs) {
+  if (replay(h)) {
     hipGraphExec_t ex = graph_for(h, variant, geo ? 1 : 2);
     for (int i = 0; i < n; ++i) HIPCHECK(hipGraphLaunch(ex, h->stream));
   } else {
     for (int i = 0; i < n; ++i) enqueue_combined_iteration(h, h->stream, variant, geo);
   }
-  HIPCHECK(mvd_launch_reduce(h->d_parts, h->grid_x, h->nviews, h->d_flux, h->d_ratio, h->d_neg, h->stream));
+  reduce_stats(h, h->stream);
   h->iterations += n;
 }
 
@@ -1905,6 +2278,7 @@ void set_psfs_impl(mvd_handle* h, const float* const* psfs, const int* psf_dims,
   }
   for (int v = 0; v < N; ++v) upload_kernel(h, B, B.P[v], B.H[ROLE_P] + (size_t)v * B.h_elems * 2);
   for (int r = 1; r < N_ROLES; ++r) h->built[r] = false;
+  for (bool& k : h->k2_built) k = false;
   build_jobs(h);
 }
 
@@ -2357,7 +2731,7 @@ int mvd_view_update(mvd_handle* h, int view, int variant) {
   return guard(h, [&] {
     if (view < 0 || view >= h->nviews) bad("view index out of range");
     h->rec_token = 0;
-    prepare_run(h, variant);
+    prepare_run(h, variant, 0);
     enqueue_view(h, h->stream, variant, view);
   });
 }
@@ -2371,7 +2745,7 @@ int mvd_profile(mvd_handle* h, int n, int variant, double* avg_ms, int* calls) {
     if (n < 1) bad("n must be >= 1");
     if (!avg_ms || !calls) bad("avg_ms and calls are required");
     h->rec_token = 0;
-    prepare_run(h, variant);
+    prepare_run(h, variant, n, true);
     PassTimer t;
     t.s = h->stream;
     for (int i = 0; i < n; ++i) enqueue_iteration(h, h->stream, variant, &t);
@@ -2456,7 +2830,21 @@ int mvd_set_tiles(mvd_handle* h, int cfg_x, int cfg_y, int cfg_z) {
     g_err = "handle is NULL";
     return MVD_EINVAL;
   }
-  return guard(h, [&] { set_tiles(h, cfg_x, cfg_y, cfg_z); });
+  return guard(h, [&] {
+    set_tiles(h, cfg_x, cfg_y, cfg_z);
+    h->tiles_chosen = true;
+  });
+}
+
+int mvd_default_tiles(mvd_handle* h) {
+  if (!h) {
+    g_err = "handle is NULL";
+    return MVD_EINVAL;
+  }
+  return guard(h, [&] {
+    set_tiles(h, pick_cfg(h, PASS_X), pick_cfg(h, PASS_Y), pick_cfg(h, PASS_Z));
+    h->tiles_chosen = false;
+  });
 }
 
 int mvd_set_schedule(mvd_handle* h, int schedule) {

@@ -72,6 +72,50 @@ struct JobDesc {
   int ex, ey, ez;
 };
 
+// Two-pass form of a convolution (mvd_two_pass.h).  The y transform of a
+// block is split as ny = R n1, y = y1 + m n1, ky = R k1 + j: the x passes do
+// the R-point transforms over m (and their twiddles) on the rows they hold
+// anyway, and one plane pass per (kx, j) does everything else of the
+// convolution (z and n1-point y transforms, product, inverses) on an
+// [nz][n1] plane that fits in LDS.  The spectrum between the passes is
+// [kx <= M][j][z][y1] complex; kernel spectra are
+// [view][kx <= M][j][y1 position][z position], positions in the order the
+// plane pass's transforms leave them.
+#define TP_MAX_STAGES 6
+#define TP_MAX_WAVES 8  // widest workgroup of the x passes
+struct TpStage {
+  int radix;
+  int nb;           // butterflies of the stage in one line: (length / earlier radices) / radix
+  int tws;          // twiddle stride: product of the earlier radices
+  unsigned mg_nb;   // multiplier for floor(j / nb)
+};
+struct TpJob {
+  int nx, ny, nz, M, nviews;
+  int R, n1;
+  int a, atiles;            // y1 values of an x tile (its rows: a R at one z), tiles per z
+  int pl;                   // LDS pitch of a plane's z lines (odd, >= n1)
+  int tw_x, pp;             // twiddle pool: length M, exp(-2 pi i k / nx)
+  int tw_y, tw_z;           // lengths ny (its every R-th entry is the table of n1) and nz
+  int nsz, nsy;
+  TpStage sz[TP_MAX_STAGES], sy[TP_MAX_STAGES];
+  int ks, kg;               // the x tile's spectrum phases take k = (c % kg) ks + c / kg
+  unsigned mg_n1, mg_nz, mg_a, mg_kg, mg_R;  // divisions by n1, nz, a, kg and R
+  int yz_tiles;             // (M + 1) R
+  int64_t V, k2_elems;      // kernel spectrum entries per view: (M + 1) ny nz
+  float* psi;
+  float* spec;              // the block's spectrum buffer (complex)
+  const float* phi;
+  const float* w;
+  float* acc;
+  float* saved;
+  const float* K2[N_ROLES];
+  float eps, lamp;
+  // the builder's inputs: the kernel planes of JobDesc
+  const float* H[N_ROLES];
+  int64_t h_main, h_elems;
+  int Mp, kz, cz;
+};
+
 // Linear boundary: a view holds this value on the grid voxels outside the
 // volume (where it has no data); the ratio pass takes q = 1 there.  Views
 // are >= 0 on the volume, so the marker is never a measured value.

@@ -80,6 +80,7 @@ def lib():
     L.mvd_set_psfs.argtypes = [H, C.POINTER(C.c_void_p), C.POINTER(C.c_int), C.c_int]
     L.mvd_set_tiles.argtypes = [H, C.c_int, C.c_int, C.c_int]
     L.mvd_get_tiles.argtypes = [H, C.POINTER(C.c_int)]
+    L.mvd_default_tiles.argtypes = [H]
     L.mvd_tile_candidates.argtypes = [C.c_int, C.c_int, C.POINTER(C.c_int), C.c_int]
     L.mvd_tile_shape.argtypes = [C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int),
                                  C.POINTER(C.c_int)]
@@ -109,8 +110,8 @@ def lib():
                  "mvd_contributing_views", "mvd_get_estimate",
                  "mvd_set_estimate",
                  "mvd_stats", "mvd_synchronize", "mvd_destroy", "mvd_compound_kernel", "mvd_kernel_spectrum",
-                 "mvd_view_update", "mvd_profile", "mvd_set_tiles", "mvd_get_tiles", "mvd_tile_candidates",
-                 "mvd_tile_shape", "mvd_loss_grad", "mvd_backward", "mvd_set_psfs", "mvd_iterate_noalloc",
+                 "mvd_view_update", "mvd_profile", "mvd_set_tiles", "mvd_get_tiles", "mvd_default_tiles",
+                 "mvd_tile_candidates", "mvd_tile_shape", "mvd_loss_grad", "mvd_backward", "mvd_set_psfs", "mvd_iterate_noalloc",
                  "mvd_create_blocked", "mvd_blocking", "mvd_set_schedule", "mvd_get_schedule",
                  "mvd_forward_recorded", "mvd_backward_recorded", "mvd_compound_kernel_vjp"):
         getattr(L, name).restype = C.c_int
@@ -437,6 +438,11 @@ class Deconvolver:
 
     def set_tiles(self, cx, cy, cz):
         _check(lib().mvd_set_tiles(self._h, int(cx), int(cy), int(cz)), self._h)
+        return self
+
+    def default_tiles(self):
+        """Back to the launch shapes (and the form of the convolutions) at create."""
+        _check(lib().mvd_default_tiles(self._h), self._h)
         return self
 
     def grid_dims(self, block=0):
