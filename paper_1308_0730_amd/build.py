@@ -39,6 +39,7 @@ SOURCES = [
     ("mvd_tp_x_update.hip", True),
     ("mvd_tp_x_comb.hip", True),
     ("mvd_tp_plane.hip", True),
+    ("mvd_prep.hip", True),
     ("mvd_weights.hip", True),
     ("mvd_embed.hip", True),
     ("mvd_runtime.cpp", True),

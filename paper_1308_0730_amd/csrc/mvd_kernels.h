@@ -110,6 +110,43 @@ hipError_t mvd_launch_plane(const TpArgs& a, int threads, size_t lds, int v, int
 // kernel spectra of every view of a.jobs[0] (grid: its planes times its views)
 hipError_t mvd_launch_plane_kernel(const TpArgs& a, size_t lds, int role, float* out);
 
+// FP64 preparation of kernels (mvd_prep.hip).  Windows are odd and centred,
+// extents {x, y, z}.
+struct CorrJob {  // out[d] = sum_e A[e] B[d + s e]
+  const double* A;
+  const double* B;
+  double* out;
+  int a[3], b[3], o[3];
+  int s;
+};
+struct CompoundJob {  // one view
+  const double* P;
+  const double* f;     // [n][nk] partner factors
+  double* K;
+  const double* kbar;  // dL/dK: then T [n][nk] and direct [nk] are written instead of K
+  double* T;
+  double* direct;
+  int nk;
+};
+struct VjpJob {  // one view; mv of its own kernel, pw and mw [n][nk] of the others'
+  const double *direct, *mv, *pw, *mw;
+  double* g;
+  int nk;
+};
+struct PlaneJob {
+  const double* K;
+  float* out;
+  int kx, ky, kz;
+};
+int mvd_corr_groups(const int* o);
+hipError_t mvd_launch_corr(const CorrJob* jobs, int n, int max_groups, hipStream_t s);
+hipError_t mvd_launch_compound(const CompoundJob* jobs, int n, int power, double* sums, hipStream_t s);
+hipError_t mvd_launch_vjp_sum(const VjpJob* jobs, int n, int max_nk, hipStream_t s);
+size_t mvd_kernel_planes_lds(int nx, int ny, int ky);
+// tx, ty: exp(-2 pi i m / n) of nx and ny
+hipError_t mvd_launch_kernel_planes(const PlaneJob* jobs, int n, int nx, int ny, int Mp, int kzw, int64_t h_main,
+                                    double scale, int max_ky, const double2* tx, const double2* ty, hipStream_t s);
+
 // weight normalisation (mvd_weights.hip), on one block's [nviews][V] weights
 hipError_t mvd_launch_overlap_stats(const float* w, int nviews, int64_t V, unsigned* cmin,
                                     unsigned long long* csum, unsigned long long* ncov, hipStream_t s);

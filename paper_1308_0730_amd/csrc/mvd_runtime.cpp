@@ -423,6 +423,275 @@ void upload_kernel(mvd_handle* h, const Block& B, const mvdh::Kern& K, float* ds
   HIPCHECK(hipStreamSynchronize(h->stream));
 }
 
+// Scratch of one preparation on the device: a region laid out first (put
+// returns the offset of a part), then allocated, filled from a host copy of
+// its inputs and given back.  Without the memory the host code prepares.
+struct PrepScratch {
+  mvd_handle* h;
+  size_t size = 0;
+  char* base = nullptr;
+  std::vector<char> in;  // host copy of [0, in.size())
+  explicit PrepScratch(mvd_handle* hd) : h(hd) {}
+  ~PrepScratch() {
+    if (!base) return;
+    (void)hipStreamSynchronize(h->stream);
+    h->raw_free(base);
+  }
+  size_t put(size_t bytes) {
+    const size_t o = size;
+    size += (bytes + 255) & ~size_t(255);
+    return o;
+  }
+  bool alloc() {
+    base = (char*)h->raw_alloc(size);
+    return base != nullptr;
+  }
+  template <class T>
+  T* at(size_t off) const {
+    return reinterpret_cast<T*>(base + off);
+  }
+  template <class T>
+  void fill(size_t off, const T* src, size_t n) {
+    if (in.size() < off + n * sizeof(T)) in.resize(off + n * sizeof(T));
+    std::memcpy(in.data() + off, src, n * sizeof(T));
+  }
+  void upload() { HIPCHECK(hipMemcpyAsync(base, in.data(), in.size(), hipMemcpyHostToDevice, h->stream)); }
+};
+
+// The partner factors' part of a preparation: PSFs, EFF's autocorrelations
+// C_w = P_w (x) P_w* and f_vw = P_v* (x) C_w or P_v* (x) P_w in the window
+// of P_v.
+struct PrepFactors {
+  std::vector<size_t> P, C, f;                   // offsets per view
+  std::vector<std::array<int, 3>> pd, cd;        // extents
+  size_t jobs = 0;
+  int n_auto = 0, n_pair = 0, g_auto = 0, g_pair = 0;
+  double fmas = 0;
+
+  // f: whether the factors are needed; the inputs come first
+  void layout(PrepScratch& S, const std::vector<mvdh::Kern>& Ps, int variant, bool factors) {
+    const int n = (int)Ps.size();
+    int rm[3] = {0, 0, 0};
+    for (const auto& K : Ps) {
+      pd.push_back({K.kx, K.ky, K.kz});
+      for (int a = 0; a < 3; ++a) rm[a] = std::max(rm[a], pd.back()[a] / 2);
+      P.push_back(S.put(K.a.size() * sizeof(double)));
+    }
+    if (!factors) return;
+    jobs = S.put((size_t)n * (n + 1) * sizeof(CorrJob));
+    for (int w = 0; w < n; ++w) {
+      std::array<int, 3> c = pd[w];
+      if (variant == MVD_EFF)
+        for (int a = 0; a < 3; ++a) c[a] = 2 * std::min(2 * (pd[w][a] / 2), 2 * rm[a]) + 1;
+      cd.push_back(c);
+      fmas += variant == MVD_EFF ? (double)c[0] * c[1] * c[2] * Ps[w].a.size() : 0.0;
+      fmas += (double)(n - 1) * Ps[w].a.size() * Ps[w].a.size();
+    }
+  }
+  void layout_out(PrepScratch& S, const std::vector<mvdh::Kern>& Ps, int variant) {
+    const int n = (int)Ps.size();
+    for (int w = 0; w < n; ++w) {
+      C.push_back(variant == MVD_EFF ? S.put((size_t)cd[w][0] * cd[w][1] * cd[w][2] * sizeof(double)) : P[w]);
+      f.push_back(S.put((size_t)n * Ps[w].a.size() * sizeof(double)));
+    }
+  }
+  static CorrJob job(const double* A, const std::array<int, 3>& a, const double* B, const std::array<int, 3>& b,
+                     double* out, const std::array<int, 3>& o, int s) {
+    CorrJob j{A, B, out, {}, {}, {}, s};
+    for (int i = 0; i < 3; ++i) j.a[i] = a[i], j.b[i] = b[i], j.o[i] = o[i];
+    return j;
+  }
+  void fill(PrepScratch& S, const std::vector<mvdh::Kern>& Ps, int variant, bool factors) {
+    const int n = (int)Ps.size();
+    for (int v = 0; v < n; ++v) S.fill(P[v], Ps[v].a.data(), Ps[v].a.size());
+    if (!factors) return;
+    std::vector<CorrJob> js;
+    if (variant == MVD_EFF)
+      for (int w = 0; w < n; ++w) {
+        js.push_back(job(S.at<double>(P[w]), pd[w], S.at<double>(P[w]), pd[w], S.at<double>(C[w]), cd[w], 1));
+        g_auto = std::max(g_auto, mvd_corr_groups(cd[w].data()));
+      }
+    n_auto = (int)js.size();
+    for (int v = 0; v < n; ++v)
+      for (int w = 0; w < n; ++w) {
+        if (w == v) continue;
+        js.push_back(job(S.at<double>(P[v]), pd[v], S.at<double>(C[w]), cd[w],
+                         S.at<double>(f[v]) + (size_t)w * Ps[v].a.size(), pd[v], 1));
+        g_pair = std::max(g_pair, mvd_corr_groups(pd[v].data()));
+      }
+    n_pair = (int)js.size() - n_auto;
+    S.fill(jobs, js.data(), js.size());
+  }
+  void launch(PrepScratch& S) const {
+    const CorrJob* j = S.at<CorrJob>(jobs);
+    HIPCHECK(mvd_launch_corr(j, n_auto, g_auto, S.h->stream));
+    HIPCHECK(mvd_launch_corr(j + n_auto, n_pair, g_pair, S.h->stream));
+  }
+};
+
+// Correlations above this many FMAs (about a quarter of a second) stay with
+// the host's separable transforms, whose work grows more slowly.
+constexpr double kPrepMaxFmas = 4e11;
+
+// Kernel planes of every view on the device (variant MVD_RL: the PSFs'
+// own); false if the kernels are beyond its limits or the memory is not there.
+bool device_planes(mvd_handle* h, const Block& B, int variant, float* dst) {
+  const int n = h->nviews;
+  const auto& Ps = B.P;
+  const bool factors = n > 1 && (variant == MVD_EFF || variant == MVD_OPT1);
+  int ky = 1;
+  for (const auto& K : Ps) ky = std::max(ky, K.ky);
+  if (mvd_kernel_planes_lds(B.nx, B.ny, ky) > (size_t)64 << 10) return false;
+  PrepScratch S(h);
+  PrepFactors F;
+  F.layout(S, Ps, variant, factors);
+  if (F.fmas > kPrepMaxFmas) return false;
+  const size_t o_comp = S.put(n * sizeof(CompoundJob)), o_plane = S.put(n * sizeof(PlaneJob));
+  const size_t o_tx = S.put(B.nx * sizeof(double2)), o_ty = S.put(B.ny * sizeof(double2));
+  const size_t o_sums = S.put(n * sizeof(double));
+  if (factors) F.layout_out(S, Ps, variant);
+  std::vector<size_t> o_K;
+  if (variant != MVD_RL)
+    for (const auto& K : Ps) o_K.push_back(S.put(K.a.size() * sizeof(double)));
+  if (!S.alloc()) return false;
+  F.fill(S, Ps, variant, factors);
+  std::vector<CompoundJob> cj(n);
+  std::vector<PlaneJob> pj(n);
+  for (int v = 0; v < n; ++v) {
+    const double* P = S.at<double>(F.P[v]);
+    double* K = variant == MVD_RL ? nullptr : S.at<double>(o_K[v]);
+    cj[v] = {P, factors ? S.at<double>(F.f[v]) : nullptr, K, nullptr, nullptr, nullptr, (int)Ps[v].a.size()};
+    pj[v] = {K ? K : P, dst + (size_t)v * B.h_elems * 2, Ps[v].kx, Ps[v].ky, Ps[v].kz};
+  }
+  S.fill(o_comp, cj.data(), n);
+  S.fill(o_plane, pj.data(), n);
+  S.fill(o_tx, mvdh::twiddles(B.nx).data(), B.nx);
+  S.fill(o_ty, mvdh::twiddles(B.ny).data(), B.ny);
+  S.upload();
+  std::vector<double> sums(n, 1.0);
+  if (variant != MVD_RL) {
+    if (factors) F.launch(S);
+    // one view: the mirrored PSF itself
+    HIPCHECK(mvd_launch_compound(S.at<CompoundJob>(o_comp), n, variant == MVD_OPT2 && n > 1, S.at<double>(o_sums),
+                                 h->stream));
+    HIPCHECK(hipMemcpyAsync(sums.data(), S.at<double>(o_sums), n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+  }
+  HIPCHECK(mvd_launch_kernel_planes(S.at<PlaneJob>(o_plane), n, B.nx, B.ny, B.Mp, B.kz, B.h_main,
+                                    1.0 / (double)B.V, ky, S.at<double2>(o_tx), S.at<double2>(o_ty), h->stream));
+  HIPCHECK(hipStreamSynchronize(h->stream));
+  for (double x : sums)
+    if (!(x > 0) || !std::isfinite(x)) throw std::invalid_argument("kernel sum must be positive");
+  return true;
+}
+
+// Kernel planes of every view of a block for a role.
+void build_planes(mvd_handle* h, const Block& B, int variant, float* dst) {
+  for (const auto& K : B.P)
+    if (K.kz > B.kz || (B.kz - K.kz) % 2) bad("kernel does not fit the z window");
+  if (device_planes(h, B, variant, dst)) return;
+  const auto K = variant == MVD_RL ? B.P : mvdh::compound_kernels(B.P, variant);
+  for (int v = 0; v < h->nviews; ++v) upload_kernel(h, B, K[v], dst + (size_t)v * B.h_elems * 2);
+}
+
+// dL/dP_w of every view from dL/dK_v of every view (EFF, OPT1) on the device:
+// with T_vw = dL/df_vw, the correlations of T_vw with the other operands of
+// f_vw (Q_vw = T_vw (x) P_v* mirrored goes into both terms of EFF).  False as
+// device_planes.
+bool device_compound_vjp(mvd_handle* h, const Block& B, int variant, const std::vector<std::vector<double>>& Kbar,
+                         std::vector<std::vector<double>>& g) {
+  const int n = h->nviews;
+  const auto& Ps = B.P;
+  if (n < 2 || (variant != MVD_EFF && variant != MVD_OPT1)) return false;
+  const bool eff = variant == MVD_EFF;
+  PrepScratch S(h);
+  PrepFactors F;
+  F.layout(S, Ps, variant, true);
+  std::vector<size_t> o_kbar, o_T, o_dir, o_mv, o_pw, o_mw, o_g;
+  std::vector<std::array<int, 3>> qd((size_t)n * n);
+  std::vector<size_t> o_Q((size_t)n * n);
+  for (int v = 0; v < n; ++v) o_kbar.push_back(S.put(Ps[v].a.size() * sizeof(double)));
+  const size_t o_comp = S.put(n * sizeof(CompoundJob)), o_sum = S.put(n * sizeof(VjpJob));
+  const size_t o_j1 = S.put((size_t)2 * n * n * sizeof(CorrJob)), o_j2 = S.put((size_t)2 * n * n * sizeof(CorrJob));
+  const size_t o_sums = S.put(n * sizeof(double));
+  F.layout_out(S, Ps, variant);
+  size_t gsz = 0;
+  for (int v = 0; v < n; ++v) {
+    const size_t nk = Ps[v].a.size(), all = (size_t)n * nk * sizeof(double);
+    o_T.push_back(S.put(all)), o_dir.push_back(S.put(nk * sizeof(double)));
+    o_mv.push_back(S.put(all)), o_pw.push_back(S.put(all)), o_mw.push_back(eff ? S.put(all) : 0);
+    gsz += nk;
+    for (int w = 0; w < n; ++w) {
+      auto& q = qd[(size_t)v * n + w];
+      // OPT1: Q is the gradient on the window of P_w itself; EFF: where both
+      // T (x) P_v* and the correlation with P_w reach
+      for (int a = 0; a < 3; ++a)
+        q[a] = eff ? 2 * std::min(2 * (F.pd[v][a] / 2), 2 * (F.pd[w][a] / 2)) + 1 : F.pd[w][a];
+      const double qn = (double)q[0] * q[1] * q[2];
+      if (v == w) continue;
+      F.fmas += nk * (qn + (double)nk) + (eff ? 2 * qn * Ps[w].a.size() : 0.0);
+      if (eff) o_Q[(size_t)v * n + w] = S.put((size_t)qn * sizeof(double));
+    }
+  }
+  const size_t o_gall = S.put(gsz * sizeof(double));
+  if (F.fmas > kPrepMaxFmas || !S.alloc()) return false;
+  F.fill(S, Ps, variant, true);
+  std::vector<CompoundJob> cj(n);
+  std::vector<VjpJob> vj(n);
+  std::vector<CorrJob> j1, j2;
+  int g1 = 0, g2 = 0, max_nk = 0;
+  size_t go = 0;
+  for (int v = 0; v < n; ++v) {
+    const size_t nk = Ps[v].a.size();
+    max_nk = std::max(max_nk, (int)nk);
+    S.fill(o_kbar[v], Kbar[v].data(), nk);
+    cj[v] = {S.at<double>(F.P[v]), S.at<double>(F.f[v]), nullptr, S.at<double>(o_kbar[v]), S.at<double>(o_T[v]),
+             S.at<double>(o_dir[v]), (int)nk};
+    vj[v] = {S.at<double>(o_dir[v]), S.at<double>(o_mv[v]), S.at<double>(o_pw[v]),
+             eff ? S.at<double>(o_mw[v]) : nullptr, S.at<double>(o_gall) + go, (int)nk};
+    go += nk;
+    for (int w = 0; w < n; ++w) {
+      if (w == v) continue;
+      const double* T = S.at<double>(o_T[v]) + (size_t)w * nk;
+      const size_t nw = Ps[w].a.size();
+      double* pw = S.at<double>(o_pw[w]) + (size_t)v * nw;
+      const auto& q = qd[(size_t)v * n + w];
+      double* Q = eff ? S.at<double>(o_Q[(size_t)v * n + w]) : pw;
+      // T with the partner operand (mirrored back: the gradient of P_v)
+      j1.push_back(PrepFactors::job(T, F.pd[v], S.at<double>(F.C[w]), F.cd[w],
+                                    S.at<double>(o_mv[v]) + (size_t)w * nk, F.pd[v], 1));
+      // T with P_v*
+      j1.push_back(PrepFactors::job(T, F.pd[v], S.at<double>(F.P[v]), F.pd[v], Q, q, -1));
+      g1 = std::max({g1, mvd_corr_groups(F.pd[v].data()), mvd_corr_groups(q.data())});
+      if (eff) {
+        j2.push_back(PrepFactors::job(Q, q, S.at<double>(F.P[w]), F.pd[w], pw, F.pd[w], -1));
+        j2.push_back(PrepFactors::job(Q, q, S.at<double>(F.P[w]), F.pd[w],
+                                      S.at<double>(o_mw[w]) + (size_t)v * nw, F.pd[w], 1));
+        g2 = std::max(g2, mvd_corr_groups(F.pd[w].data()));
+      }
+    }
+  }
+  S.fill(o_comp, cj.data(), n);
+  S.fill(o_sum, vj.data(), n);
+  S.fill(o_j1, j1.data(), j1.size());
+  if (eff) S.fill(o_j2, j2.data(), j2.size());
+  S.upload();
+  F.launch(S);
+  HIPCHECK(mvd_launch_compound(S.at<CompoundJob>(o_comp), n, 0, S.at<double>(o_sums), h->stream));
+  HIPCHECK(mvd_launch_corr(S.at<CorrJob>(o_j1), (int)j1.size(), g1, h->stream));
+  HIPCHECK(mvd_launch_corr(S.at<CorrJob>(o_j2), (int)j2.size(), g2, h->stream));
+  HIPCHECK(mvd_launch_vjp_sum(S.at<VjpJob>(o_sum), n, max_nk, h->stream));
+  std::vector<double> all(gsz);
+  HIPCHECK(hipMemcpyAsync(all.data(), S.at<double>(o_gall), gsz * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+  HIPCHECK(hipStreamSynchronize(h->stream));
+  g.resize(n);
+  size_t o = 0;
+  for (int v = 0; v < n; ++v) {
+    g[v].assign(all.begin() + o, all.begin() + o + Ps[v].a.size());
+    o += Ps[v].a.size();
+  }
+  return true;
+}
+
 bool cfg_fits(const mvd_handle* h, int kind, int c);
 
 // Default launch shape of a pass kind: a forced candidate if it fits, else
@@ -1122,7 +1391,7 @@ void create_impl(mvd_handle* h, int nb, const mvd_problem* ps, const mvd_options
     set_kernel_window(B);
     B.kz_cap = B.kz;
     B.H[ROLE_P] = (float*)h->dalloc((size_t)N * B.h_elems * 2 * sizeof(float));
-    for (int v = 0; v < N; ++v) upload_kernel(h, B, B.P[v], B.H[ROLE_P] + (size_t)v * B.h_elems * 2);
+    build_planes(h, B, MVD_RL, B.H[ROLE_P]);
     add_plans(h, B, plans, tw);
     HIPCHECK(mvd_launch_fill(B.psi, B.V, (float)B.s, h->stream));
   }
@@ -1288,7 +1557,7 @@ void create_blocked_impl(mvd_handle* h, const mvd_problem* p, const mvd_options*
     B.kz_cap = B.kz;
     if (b == 0) {
       B.H[ROLE_P] = (float*)h->dalloc((size_t)N * B.h_elems * 2 * sizeof(float));
-      for (int v = 0; v < N; ++v) upload_kernel(h, B, B.P[v], B.H[ROLE_P] + (size_t)v * B.h_elems * 2);
+      build_planes(h, B, MVD_RL, B.H[ROLE_P]);
     } else {
       B.H[ROLE_P] = h->blocks[0].H[ROLE_P];
     }
@@ -1307,8 +1576,7 @@ void ensure_role(mvd_handle* h, int role) {
       continue;
     }
     if (!B.H[role]) B.H[role] = (float*)h->dalloc((size_t)h->nviews * B.h_elems * 2 * sizeof(float));
-    const auto K = mvdh::compound_kernels(B.P, variant);
-    for (int v = 0; v < h->nviews; ++v) upload_kernel(h, B, K[v], B.H[role] + (size_t)v * B.h_elems * 2);
+    build_planes(h, B, variant, B.H[role]);
   }
   build_jobs(h);
   h->built[role] = true;
@@ -2121,7 +2389,9 @@ void grad_reverse_impl(mvd_handle* h, double* const* grad_psf, float* grad_psi0,
         t.a = window_of(h->g_acck + (size_t)v * S, B.P[v]);
         Kbar[v] = mvdh::mirror(t).a;
       }
-      const auto add = mvdh::compound_kernels_vjp(B.P, h->rec_variant, Kbar);
+      std::vector<std::vector<double>> add;
+      if (!device_compound_vjp(h, B, h->rec_variant, Kbar, add))
+        add = mvdh::compound_kernels_vjp(B.P, h->rec_variant, Kbar);
       for (int w = 0; w < N; ++w)
         for (size_t j = 0; j < add[w].size(); ++j) gP[w][j] += add[w][j];
     }
@@ -2276,7 +2546,7 @@ void set_psfs_impl(mvd_handle* h, const float* const* psfs, const int* psf_dims,
     for (int r = 0; r < N_ROLES; ++r) B.H[r] = nullptr;
     B.H[ROLE_P] = (float*)h->dalloc((size_t)N * B.h_elems * 2 * sizeof(float));
   }
-  for (int v = 0; v < N; ++v) upload_kernel(h, B, B.P[v], B.H[ROLE_P] + (size_t)v * B.h_elems * 2);
+  build_planes(h, B, MVD_RL, B.H[ROLE_P]);
   for (int r = 1; r < N_ROLES; ++r) h->built[r] = false;
   for (bool& k : h->k2_built) k = false;
   build_jobs(h);
@@ -2484,10 +2754,11 @@ void* scratch_on_current_device() {
 
 // Bump allocation over the scratch array (the handle's allocator callbacks;
 // dalloc rounds every request up to 256 bytes, so every buffer stays
-// 256-byte aligned).  Nothing is freed: the region is reused by the next run.
+// 256-byte aligned).  Only the last buffer can be given back (preparations do);
+// the region is reused by the next run.
 struct ScratchArena {
   unsigned char* base;
-  size_t cap, used, refused;
+  size_t cap, used, refused, last;
 };
 
 void* arena_alloc(size_t bytes, void* ctx) {
@@ -2497,11 +2768,15 @@ void* arena_alloc(size_t bytes, void* ctx) {
     return nullptr;
   }
   void* p = a->base + a->used;
+  a->last = a->used;
   a->used += bytes;
   return p;
 }
 
-void arena_free(void*, void*) {}
+void arena_free(void* p, void* ctx) {
+  auto* a = static_cast<ScratchArena*>(ctx);
+  if (a->used > a->last && p == a->base + a->last) a->used = a->last;
+}
 
 void iterate_noalloc_impl(const mvd_problem* p, const mvd_options* o, const float* psi0, int n, int variant,
                           float* psi_out) {
@@ -2512,7 +2787,7 @@ void iterate_noalloc_impl(const mvd_problem* p, const mvd_options* o, const floa
   if (o && (o->alloc || o->free)) bad("the no-allocation run takes no allocator callbacks");
   mvd_options opt{};
   if (o) opt = *o;
-  ScratchArena arena{static_cast<unsigned char*>(scratch_on_current_device()), MVD_NOALLOC_SCRATCH_BYTES, 0, 0};
+  ScratchArena arena{static_cast<unsigned char*>(scratch_on_current_device()), MVD_NOALLOC_SCRATCH_BYTES, 0, 0, 0};
   opt.alloc = arena_alloc;
   opt.free = arena_free;
   opt.alloc_ctx = &arena;
@@ -2526,14 +2801,18 @@ void iterate_noalloc_impl(const mvd_problem* p, const mvd_options* o, const floa
     const int nonfinite = get_estimate_impl(&h, psi_out, MVD_MEM_DEVICE, 0);
     h.release();
     if (nonfinite) throw Error(MVD_ENONFINITE, "the estimate became non-finite");
-  } catch (...) {
+  } catch (const Error& e) {
     // nothing queued may outlive the call: the next run reuses the region
     (void)hipStreamSynchronize(h.stream);
     h.release();
-    if (arena.refused)
+    if (e.code == MVD_ENOMEM && arena.refused)
       bad("the problem needs more device memory than the no-allocation run's scratch array holds (" +
           std::to_string(MVD_NOALLOC_SCRATCH_BYTES) + " bytes; a request of " + std::to_string(arena.refused) +
           " bytes with " + std::to_string(arena.used) + " in use)");
+    throw;
+  } catch (...) {
+    (void)hipStreamSynchronize(h.stream);
+    h.release();
     throw;
   }
 }
