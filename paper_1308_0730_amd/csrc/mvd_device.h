@@ -13,11 +13,15 @@ namespace mvdk {
 // writes the spectrum in ascending z and the y pass after them reads it in
 // ascending z, so each reader starts on the planes written last, which are
 // still held by the memory-side cache (the 256 MB Infinity Cache holds most
-// of an embryo-sized spectrum).
+// of an embryo-sized spectrum).  With last_job_first the jobs are taken from
+// the last, each in ascending tiles: the z passes of several jobs start on
+// the job that the forward y pass wrote last and end on the one that the
+// inverse y pass reads first.
 __device__ __forceinline__ int find_job(const JobDesc* __restrict__ jobs, int njobs, int kind,
-                                        int param, int& local, bool reverse = false) {
+                                        int param, int& local, bool reverse = false, bool last_job_first = false) {
   int t = reverse ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;
-  for (int j = 0; j < njobs; ++j) {
+  for (int i = 0; i < njobs; ++i) {
+    const int j = last_job_first ? njobs - 1 - i : i;
     const int c = mvd_tiles(jobs[j], kind, param);
     if (t < c) {
       local = t;
