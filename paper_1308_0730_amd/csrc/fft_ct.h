@@ -168,10 +168,17 @@ struct DivC {
   }
 };
 
-// Line and butterfly of work item `it` (< NL * NB rounded up to whole rounds).
-template <int NL, int NB, int MAXIT, bool LF>
+// Line and butterfly of work item `it` (< NL * NB rounded up to whole
+// rounds).  P24: by DivC, as the column passes and the two-pass x passes do;
+// the four-pass rows keep the plain operators, with which the update pass
+// fits more waves (400 points: 109 us against 138 by DivC, 200 points 56
+// against 64).
+template <int NL, int NB, int MAXIT, bool LF, bool P24>
 __device__ __forceinline__ void item_of(int it, int& line, int& j) {
-  if constexpr (LF) {
+  if constexpr (!P24) {
+    line = LF ? it % NL : it / NB;
+    j = LF ? it / NL : it % NB;
+  } else if constexpr (LF) {
     line = DivC<NL, MAXIT>::mod(it);
     j = DivC<NL, MAXIT>::div(it);
   } else {
@@ -221,7 +228,7 @@ __device__ __forceinline__ void ct_prefetch(int tid, const S& src, float2 (&v)[F
   for (int i = 0; i < MAXB; ++i) {
     const int it = tid + i * T;
     int line, j;
-    item_of<NL, NB, MAXB * T, LF>(it, line, j);
+    item_of<NL, NB, MAXB * T, LF, true>(it, line, j);
     if ((TOTAL % T == 0) || it < TOTAL) {
 #pragma unroll
       for (int r = 0; r < R; ++r) v[i][r] = src.ld(line, j + r * NB);
@@ -238,6 +245,7 @@ __device__ __forceinline__ void ct_stage(int tid_in, const float2* tw, const S& 
   constexpr int MAXB = (TOTAL + T - 1) / T;
   constexpr int TWS = L / (NS * R);
   constexpr bool FULL = TOTAL % T == 0;
+  constexpr bool P24 = SY != SYNC_WAVE;
   int tid = tid_in;
   asm volatile("" : "+v"(tid));
   float2 v[MAXB][R];
@@ -246,7 +254,7 @@ __device__ __forceinline__ void ct_stage(int tid_in, const float2* tw, const S& 
   for (int i = 0; i < MAXB; ++i) {
     const int it = tid + i * T;
     int line, j;
-    item_of<NL, NB, MAXB * T, LF>(it, line, j);
+    item_of<NL, NB, MAXB * T, LF, P24>(it, line, j);
     ln[i] = line;
     jb[i] = j;
     if (FULL || it < TOTAL) {
@@ -265,17 +273,21 @@ __device__ __forceinline__ void ct_stage(int tid_in, const float2* tw, const S& 
     const int it = tid + i * T;
     if (FULL || it < TOTAL) {
       const int j = jb[i];
-      const int k = DivC<NS, NB>::mod(j);
+      int k;
+      if constexpr (P24)
+        k = DivC<NS, NB>::mod(j);
+      else
+        k = j % NS;
       if (NS > 1) {
 #pragma unroll
         for (int r = 1; r < R; ++r) {
-          float2 w = tw[__umul24((unsigned)k, r * TWS)];
+          float2 w = tw[P24 ? (int)__umul24((unsigned)k, r * TWS) : k * r * TWS];
           if (INV) w.y = -w.y;
           v[i][r] = cmul(v[i][r], w);
         }
       }
       Dft<R, INV>::run(v[i]);
-      const int base = (int)__umul24((unsigned)(j - k), R) + k;
+      const int base = (P24 ? (int)__umul24((unsigned)(j - k), R) : (j - k) * R) + k;
 #pragma unroll
       for (int r = 0; r < R; ++r) dst.st(ln[i], base + r * NS, v[i][r], i, r);
     }
@@ -324,14 +336,14 @@ struct LastRadix<R> {
 // Output positions of the last stage: butterfly slot i of this thread writes
 // output r to position j + r * (L / RL) of line `line` (the last stage's
 // butterflies have j < L / RL = NS, so k = j).
-template <int L, int RL, int T, int NL, bool LF>
+template <int L, int RL, int T, int NL, bool LF, bool P24 = LF>
 struct LastMap {
   static constexpr int NB = L / RL;
   static constexpr int TOTAL = NB * NL;
   static constexpr int MAXB = (TOTAL + T - 1) / T;
   static __device__ __forceinline__ bool at(int tid, int i, int& line, int& j) {
     const int it = tid + i * T;
-    item_of<NL, NB, MAXB * T, LF>(it, line, j);
+    item_of<NL, NB, MAXB * T, LF, P24>(it, line, j);
     return (TOTAL % T == 0) || it < TOTAL;
   }
 };

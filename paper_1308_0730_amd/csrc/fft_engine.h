@@ -142,10 +142,8 @@ template <int PITCH>
 struct LdsRow {
   float2* p;
   static constexpr bool lds = true;
-  __device__ __forceinline__ float2 ld(int line, int pos) const { return p[__umul24((unsigned)line, PITCH) + pos]; }
-  __device__ __forceinline__ void st(int line, int pos, float2 v) const {
-    p[__umul24((unsigned)line, PITCH) + pos] = v;
-  }
+  __device__ __forceinline__ float2 ld(int line, int pos) const { return p[line * PITCH + pos]; }
+  __device__ __forceinline__ void st(int line, int pos, float2 v) const { p[line * PITCH + pos] = v; }
 };
 
 // Global tile: element (line, pos) at base[line * ls + pos * ps] (32-bit
@@ -166,7 +164,9 @@ struct GTile {
 
 // ---- synchronisation ---------------------------------------------------------
 
-enum { SYNC_BLOCK = 0, SYNC_WAVE = 1 };
+// SYNC_WAVE24: one wavefront, with the compile-time stages' indices by 24-bit
+// products (see DivC).
+enum { SYNC_BLOCK = 0, SYNC_WAVE = 1, SYNC_WAVE24 = 2 };
 
 template <int SY>
 __device__ __forceinline__ void gsync() {

@@ -96,6 +96,21 @@ def row_radices(M):
     return radices(M, big=8, merge=False)
 
 
+def row_forward_radices(M):
+    """Radices of the modes without an update epilogue (forward, ratio) at
+    the same rows per wave: composite ones between 256 and 512 points where
+    the cost model of the two-pass rows saves 8 % or more (432 points: 9 x 6 x 8
+    instead of 4 x 4 x 3 x 3 x 3).  Rows this long fill a large radix's stage
+    without further rows per wave.  The update passes, which hold two
+    operands, keep the small radices: the larger ones take them past 128
+    registers."""
+    small, rpw = row_radices(M), row_rows(M)
+    if not 256 < M <= 512:
+        return small
+    best = min((s for s in row_sequences(M) if 16 not in s), key=lambda s: (row_cost(M, rpw, s), len(s), s))
+    return best if row_cost(M, rpw, best) < 0.92 * row_cost(M, rpw, small) else small
+
+
 def row_rows(M):
     """Rows per wave: enough for the largest-radix stage to give nearly every
     lane a butterfly; where that count does not fill exactly one round of
@@ -153,33 +168,33 @@ TP_MAX_ROW = 256
 DFT_OPS = {2: 4, 3: 14, 4: 16, 5: 36, 6: 46, 8: 56, 9: 100, 10: 108, 12: 122, 15: 210, 16: 170}
 
 
-def tp_row_plan(M):
-    best = None
-
-    def seqs(n, cur):
-        if n == 1:
-            yield cur
-            return
-        if len(cur) >= 5:
-            return
+def row_sequences(M, n=None, cur=()):
+    n = M if n is None else n
+    if n == 1:
+        yield list(cur)
+    elif len(cur) < 5:
         for r in DFT_OPS:
             if n % r == 0:
-                yield from seqs(n // r, cur + [r])
+                yield from row_sequences(M, n // r, cur + (r,))
 
-    for seq in seqs(M, []):
+
+def row_cost(M, rpw, seq):
+    """Modelled work per row: rounds of 64 butterflies of every stage."""
+    cost = sum(-(-(M // r) * rpw // 64) * (DFT_OPS[r] + (4 * (r - 1) if i else 0) + 3 * r + 8)
+               for i, r in enumerate(seq))
+    return cost / rpw
+
+
+def tp_row_plan(M):
+    best = None
+    for seq in row_sequences(M):
         for rpw in range(1, 17):
             if -(-M * rpw // 64) > 10:
                 break
-            cost = 0
-            regs = 0
-            for i, r in enumerate(seq):
-                slots = -(-(M // r) * rpw // 64)
-                regs = max(regs, slots * r)
-                cost += slots * (DFT_OPS[r] + (4 * (r - 1) if i else 0) + 3 * r + 8)
-            if regs > 16:
+            if max(-(-(M // r) * rpw // 64) * r for r in seq) > 16:
                 continue
-            # per row; fewer rows per wave (more waves) on a near tie
-            key = (round(cost / rpw * (1 + 0.004 * rpw), 3), len(seq))
+            # fewer rows per wave (more waves) on a near tie
+            key = (round(row_cost(M, rpw, seq) * (1 + 0.004 * rpw), 3), len(seq))
             if best is None or key < best[0]:
                 best = (key, rpw, seq)
     return best[1], best[2]
@@ -209,6 +224,11 @@ def main():
         end = " \\" if i + 1 < len(tps) else ""
         rpw, rad = tp_row_plan(M)
         lines.append(f"  X({M}, {rpw}, {', '.join(map(str, rad))}){end}")
+    lines += ["", "// X(M, waves per workgroup, rows per wave, radices...) of the forward and ratio modes",
+              "#define MVD_EXACT_ROW_FWD(X) \\"]
+    for i, M in enumerate(rows):
+        end = " \\" if i + 1 < len(rows) else ""
+        lines.append(f"  X({M}, 4, {row_rows(M)}, {', '.join(map(str, row_forward_radices(M)))}){end}")
     lines.append("")
     # column length classes: the per-length plans of one thread count and
     # length range, for kernels that serve blocks of several lengths

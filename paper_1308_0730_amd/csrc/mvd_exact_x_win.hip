@@ -6,27 +6,37 @@
 
 using namespace mvdk;
 
+#define XK(md, m, wpb, rpw, ...)                                                                               \
+  k_xpass_ct<md, wpb, rpw, m, __VA_ARGS__><<<a.grid, 64 * wpb, 0, a.stream>>>(a.jobs, a.njobs, a.plans, a.tw, \
+                                                                             v, parts, flags, opt)
+
+// forward windows with the forward plans, updates with the small radices (see
+// mvd_exact_x.hip)
+static hipError_t launch_forward(const LaunchArgs& a, int M, int v, Partial* parts, int* flags, int opt) {
+  switch (M) {
+#define X(m, wpb, rpw, ...)          \
+  case m:                            \
+    XK(8, m, wpb, rpw, __VA_ARGS__); \
+    break;
+    MVD_EXACT_ROW_FWD(X)
+#undef X
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t mvd_launch_x_exact_win(const LaunchArgs& a, int M, int mode, int v, Partial* parts, int* flags,
                                   int opt) {
+  if (mode == 8) return launch_forward(a, M, v, parts, flags, opt);
+  if (mode != 10) return hipErrorInvalidValue;
   switch (M) {
-#define XM(md, m, wpb, rpw, ...)                                                                         \
-  case md:                                                                                               \
-    k_xpass_ct<md, wpb, rpw, m, __VA_ARGS__><<<a.grid, 64 * wpb, 0, a.stream>>>(a.jobs, a.njobs, a.plans, \
-                                                                               a.tw, v, parts, flags,    \
-                                                                               opt);                     \
-    break;
-#define X(m, wpb, rpw, ...)               \
-  case m:                                 \
-    switch (mode) {                       \
-      XM(8, m, wpb, rpw, __VA_ARGS__)     \
-      XM(10, m, wpb, rpw, __VA_ARGS__)    \
-      default:                            \
-        return hipErrorInvalidValue;      \
-    }                                     \
+#define X(m, wpb, rpw, ...)           \
+  case m:                             \
+    XK(10, m, wpb, rpw, __VA_ARGS__); \
     break;
     MVD_EXACT_ROW(X)
 #undef X
-#undef XM
     default:
       return hipErrorInvalidValue;
   }

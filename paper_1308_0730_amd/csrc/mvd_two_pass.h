@@ -403,6 +403,17 @@ struct TpOp {
   }
 };
 
+// A wave's rows in LDS.
+template <int PITCH>
+struct TpRow {
+  float2* p;
+  static constexpr bool lds = true;
+  __device__ __forceinline__ float2 ld(int line, int pos) const { return p[__umul24((unsigned)line, PITCH) + pos]; }
+  __device__ __forceinline__ void st(int line, int pos, float2 v) const {
+    p[__umul24((unsigned)line, PITCH) + pos] = v;
+  }
+};
+
 #define TP_SPLITS(X) X(1) X(2) X(3) X(4) X(5) X(6) X(8) X(9)
 
 template <int MODE, int RPW, int M, int... Rs>
@@ -411,7 +422,7 @@ __global__ void __launch_bounds__(64 * TP_MAX_WAVES)
                Partial* __restrict__ parts, int* __restrict__ flags, int opt) {
   constexpr int PM = tp_row_pitch(M);
   constexpr int RL = LastRadix<Rs...>::value;
-  using LM = LastMap<M, RL, 64, RPW, false>;
+  using LM = LastMap<M, RL, 64, RPW, false, true>;
   extern __shared__ float2 dyn[];
   __shared__ double rf[TP_MAX_WAVES];
   __shared__ unsigned rc[TP_MAX_WAVES];
@@ -445,7 +456,7 @@ __global__ void __launch_bounds__(64 * TP_MAX_WAVES)
     s_wr[i] = ldg(twp + J.tw_y + (e < J.ny ? e : 0));
   }
   float2* spec = reinterpret_cast<float2*>(J.spec);
-  const LdsRow<PM> L{dyn + wave * RPW * PM};
+  const TpRow<PM> L{dyn + wave * RPW * PM};
   const bool first = opt & XOPT_FIRST, geo = opt & XOPT_GEO;
   double flux = 0.0;
   unsigned ncr = 0, ncn = 0;
@@ -469,8 +480,8 @@ __global__ void __launch_bounds__(64 * TP_MAX_WAVES)
       for (int r = 0; r < R1; ++r) in[i][r] = o >= 0 ? ld2(J.psi + o + 2 * (j + r * NB)) : make_float2(0.f, 0.f);
     }
     __syncthreads();  // tables
-    Plain<LdsRow<PM>> out{L};
-    CtRun<false, M, 64, RPW, false, SYNC_WAVE, 1, true, Rs...>::run(lane, s_tw, RegSrc<MB, R1>{in}, L, out);
+    Plain<TpRow<PM>> out{L};
+    CtRun<false, M, 64, RPW, false, SYNC_WAVE24, 1, true, Rs...>::run(lane, s_tw, RegSrc<MB, R1>{in}, L, out);
   } else {
     // operands of the pointwise step, in the order the last inverse stage
     // produces its outputs
@@ -501,14 +512,14 @@ __global__ void __launch_bounds__(64 * TP_MAX_WAVES)
     __syncthreads();
     TpOp<MODE, PM, LM::MAXB, RL> op{L.p,  pa,    pb,  ro,    J.psi,  J.acc, opb != nullptr, first, geo,
                                     J.eps, J.lamp, 1.f / (float)J.nviews, 0.0, 0u, 0u, false};
-    CtRun<true, M, 64, RPW, false, SYNC_WAVE, 1, true, Rs...>::run(lane, s_tw, L, L, op);
+    CtRun<true, M, 64, RPW, false, SYNC_WAVE24, 1, true, Rs...>::run(lane, s_tw, L, L, op);
     flux = op.flux;
     ncr = op.ncr;
     ncn = op.ncn;
     bad = op.bad;
     if (MODE != 3) {
-      Plain<LdsRow<PM>> out{L};
-      CtRun<false, M, 64, RPW, false, SYNC_WAVE, 1, true, Rs...>::run(lane, s_tw, L, L, out);
+      Plain<TpRow<PM>> out{L};
+      CtRun<false, M, 64, RPW, false, SYNC_WAVE24, 1, true, Rs...>::run(lane, s_tw, L, L, out);
     }
   }
   if (MODE != 3) {
