@@ -115,7 +115,7 @@ typedef void (*mvd_free_fn)(void* ptr, void* ctx);
  *              alloc returns NULL on failure, and must return 256-byte aligned memory
  *   use_graphs 0 = launch kernels directly, 1 = replay one HIP graph per
  *              iteration (default when options are NULL; handles whose
- *              blocks have different extents launch directly)
+ *              blocks have different extents replay one per stream lane)
  *   tile_config  0 = autotuned/default pass shapes; k > 0 forces candidate k-1
  *   boundary   MVD_BOUNDARY_CIRCULAR (0): the volume is one period of a
  *              periodic grid (the convolutions wrap around);

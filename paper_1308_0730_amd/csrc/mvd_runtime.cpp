@@ -133,6 +133,7 @@ struct mvd_handle {
   hipEvent_t ev_fork = nullptr;
   hipEvent_t ev_join[kSide] = {};
   bool defer_join = false;
+  int only_lane = -1;  // while one lane's chain is captured: launch its groups only
   std::vector<int> block_lane;
   JobDesc* d_jobs_k[3] = {nullptr, nullptr, nullptr};
   std::vector<int> order[3];
@@ -171,6 +172,9 @@ struct mvd_handle {
   // two-pass form, and n)
   int schedule = 0;
   std::map<std::pair<int, int>, hipGraphExec_t> run_exec;
+  // blocks on several lanes: one chain per lane (key: variant and n of a
+  // block-major run, n = 0 for a pass-major iteration)
+  std::map<std::pair<int, int>, std::vector<hipGraphExec_t>> lane_exec;
   FftPlan* d_plans = nullptr;
   float2* d_tw = nullptr;
   Partial* d_parts = nullptr;
@@ -271,6 +275,10 @@ struct mvd_handle {
       }
     for (auto& kv : run_exec) (void)hipGraphExecDestroy(kv.second);
     run_exec.clear();
+    if (!lane_exec.empty()) (void)hipDeviceSynchronize();
+    for (auto& kv : lane_exec)
+      for (auto g : kv.second) (void)hipGraphExecDestroy(g);
+    lane_exec.clear();
     if (cap) (void)hipDeviceSynchronize();
     for (void* p : tp_allocs) raw_free(p);
     tp_allocs.clear();
@@ -820,7 +828,11 @@ void build_jobs(mvd_handle* h) {
 void drop_graphs(mvd_handle* h) {
   bool any = false;
   for (auto& g : h->exec) any |= g != nullptr;
-  if (any || !h->run_exec.empty()) HIPCHECK(hipStreamSynchronize(h->stream));
+  if (any || !h->run_exec.empty() || !h->lane_exec.empty()) HIPCHECK(hipStreamSynchronize(h->stream));
+  for (int l = 0; l < h->nside && !h->lane_exec.empty(); ++l) HIPCHECK(hipStreamSynchronize(h->side[l]));
+  for (auto& kv : h->lane_exec)
+    for (auto g : kv.second) (void)hipGraphExecDestroy(g);
+  h->lane_exec.clear();
   for (auto& g : h->exec)
     if (g) {
       (void)hipGraphExecDestroy(g);
@@ -1609,6 +1621,11 @@ LaunchArgs group_args(mvd_handle* h, hipStream_t s, int kind, const mvd_handle::
 // streams were forked before the sequence and are joined after it.
 template <class F>
 void run_groups(mvd_handle* h, hipStream_t s, int kind, F&& launch) {
+  if (h->only_lane >= 0) {
+    for (const auto& g : h->groups[kind])
+      if (g.lane == h->only_lane) HIPCHECK(launch(g, s));
+    return;
+  }
   if (h->defer_join) {
     for (const auto& g : h->groups[kind]) HIPCHECK(launch(g, g.lane ? h->side[g.lane - 1] : s));
     return;
@@ -1894,28 +1911,35 @@ bool block_major(const mvd_handle* h) {
 // per lane, keep their spectra, views and estimates in the memory-side
 // cache from pass to pass.  Blocks are independent, so any such order gives
 // the same results; the lanes are forked once and joined at the end.
-void enqueue_run_blocks(mvd_handle* h, hipStream_t s, int variant, int n) {
+void enqueue_lane_blocks(mvd_handle* h, hipStream_t s, int variant, int n, int lane) {
+  std::vector<int> mine;
+  for (int b = 0; b < (int)h->blocks.size(); ++b)
+    if (h->block_lane[b] == lane) mine.push_back(b);
+  if (h->schedule == MVD_SCHEDULE_RUN_MAJOR) {
+    for (int b : mine)
+      for (int i = 0; i < n; ++i)
+        for (int v = 0; v < h->nviews; ++v) enqueue_view_block(h, s, variant, v, b);
+  } else {
+    for (int i = 0; i < n; ++i)
+      for (int b : mine)
+        for (int v = 0; v < h->nviews; ++v) enqueue_view_block(h, s, variant, v, b);
+  }
+}
+
+// f(lane, its stream) for every lane, forked from s and joined back.
+template <class F>
+void over_lanes(mvd_handle* h, hipStream_t s, F&& f) {
   HIPCHECK(hipEventRecord(h->ev_fork, s));
   for (int l = 0; l < h->nside; ++l) HIPCHECK(hipStreamWaitEvent(h->side[l], h->ev_fork, 0));
-  for (int l = 0; l <= h->nside; ++l) {
-    hipStream_t sl = l ? h->side[l - 1] : s;
-    std::vector<int> mine;
-    for (int b = 0; b < (int)h->blocks.size(); ++b)
-      if (h->block_lane[b] == l) mine.push_back(b);
-    if (h->schedule == MVD_SCHEDULE_RUN_MAJOR) {
-      for (int b : mine)
-        for (int i = 0; i < n; ++i)
-          for (int v = 0; v < h->nviews; ++v) enqueue_view_block(h, sl, variant, v, b);
-    } else {
-      for (int i = 0; i < n; ++i)
-        for (int b : mine)
-          for (int v = 0; v < h->nviews; ++v) enqueue_view_block(h, sl, variant, v, b);
-    }
-  }
+  for (int l = 0; l <= h->nside; ++l) f(l, l ? h->side[l - 1] : s);
   for (int l = 0; l < h->nside; ++l) {
     HIPCHECK(hipEventRecord(h->ev_join[l], h->side[l]));
     HIPCHECK(hipStreamWaitEvent(s, h->ev_join[l], 0));
   }
+}
+
+void enqueue_run_blocks(mvd_handle* h, hipStream_t s, int variant, int n) {
+  over_lanes(h, s, [&](int l, hipStream_t sl) { enqueue_lane_blocks(h, sl, variant, n, l); });
 }
 
 // One combined update (eq. 51): every view's back-projected ratio is taken
@@ -1996,11 +2020,13 @@ void prepare_run(mvd_handle* h, int variant, int n, bool classic = false, bool c
   h->spec_tp = two;
 }
 
-// Whether runs replay graphs: only where every block sits on one lane, so
+// Whether runs replay one graph: only where every block sits on one lane, so
 // that the graph is a chain.  A graph whose branches are the lanes of
 // uneven blocks has ended the process inside its replay (a host segmentation
-// fault, now and then, at hundreds of replays); those runs launch directly,
-// which keeps ahead of the device too.
+// fault, now and then, at hundreds of replays).  The lanes of uneven blocks
+// replay a chain each (lane_graphs_for; 48 blocks launched directly instead: 113 ms
+// per run, 102 in the branching graph), other sequences over lanes launch
+// directly.
 bool replay(const mvd_handle* h) {
   if (!h->use_graphs) return false;
   for (int l : h->block_lane)
@@ -2069,13 +2095,66 @@ hipGraphExec_t run_graph_for(mvd_handle* h, int variant, int n) {
   return ex;
 }
 
+// The chains of the lanes of uneven blocks: each lane's part of a block-major
+// run of n iterations, or (n = 0) of a pass-major iteration, as a graph of
+// its own that is launched on the lane's stream.
+const std::vector<hipGraphExec_t>& lane_graphs_for(mvd_handle* h, int variant, int n) {
+  const auto key = std::make_pair(variant, n);
+  auto it = h->lane_exec.find(key);
+  if (it != h->lane_exec.end()) return it->second;
+  if (h->lane_exec.size() >= 4) drop_graphs(h);  // bounded, as the graphs of whole runs
+  std::vector<hipGraphExec_t> ex;
+  try {
+    for (int l = 0; l <= h->nside; ++l) {
+      hipGraph_t g = nullptr;
+      HIPCHECK(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
+      h->only_lane = l;
+      try {
+        if (n)
+          enqueue_lane_blocks(h, h->cap, variant, n, l);
+        else
+          for (int v = 0; v < h->nviews; ++v) enqueue_view(h, h->cap, variant, v, nullptr);
+      } catch (...) {
+        h->only_lane = -1;
+        (void)hipStreamEndCapture(h->cap, &g);
+        if (g) (void)hipGraphDestroy(g);
+        throw;
+      }
+      h->only_lane = -1;
+      HIPCHECK(hipStreamEndCapture(h->cap, &g));
+      hipGraphExec_t e = nullptr;
+      const hipError_t rc = hipGraphInstantiate(&e, g, nullptr, nullptr, 0);
+      (void)hipGraphDestroy(g);
+      HIPCHECK(rc);
+      ex.push_back(e);
+    }
+  } catch (...) {
+    for (auto e : ex) (void)hipGraphExecDestroy(e);
+    throw;
+  }
+  return h->lane_exec[key] = ex;
+}
+
+// Whether the lanes of uneven blocks replay their chains: per-length plans
+// for every pass kind (so that every launch belongs to one lane).
+bool replay_lanes(const mvd_handle* h) {
+  if (!h->use_graphs || replay(h) || h->spec_tp) return false;
+  return h->cfg_x == mvd_exact_cfg(PASS_X) && h->cfg_y == mvd_exact_cfg(PASS_Y) && h->cfg_z == mvd_exact_cfg(PASS_Z);
+}
+
 void iterate_impl(mvd_handle* h, int n, int variant) {
   if (variant < MVD_RL || variant > MVD_OPT2) bad("variant must be MVD_RL, MVD_EFF, MVD_OPT1 or MVD_OPT2");
   if (n < 0) bad("n must be >= 0");
   if (n == 0) return;
   h->rec_token = 0;
   prepare_run(h, variant, n);
-  if (block_major(h)) {
+  if (replay_lanes(h)) {
+    const bool major = block_major(h);
+    const auto& ex = lane_graphs_for(h, variant, major ? n : 0);
+    over_lanes(h, h->stream, [&](int l, hipStream_t sl) {
+      for (int i = 0; i < (major ? 1 : n); ++i) HIPCHECK(hipGraphLaunch(ex[l], sl));
+    });
+  } else if (block_major(h)) {
     if (replay(h))
       HIPCHECK(hipGraphLaunch(run_graph_for(h, variant, n), h->stream));
     else
