@@ -235,8 +235,12 @@ class Deconvolver:
         dev = self.device
 
         def _alloc(nbytes, ctx):
+            # from the pool of the handle's stream, whichever stream is
+            # current at a lazy allocation: the caching allocator reuses a
+            # block in the order of the stream it was allocated on only
             try:
-                t = torch.empty(int(nbytes), dtype=torch.uint8, device=dev)
+                with torch.cuda.stream(self.stream):
+                    t = torch.empty(int(nbytes), dtype=torch.uint8, device=dev)
             except RuntimeError:
                 return None
             self._bufs[t.data_ptr()] = t
