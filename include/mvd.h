@@ -321,15 +321,26 @@ int mvd_set_psfs(mvd_handle* h, const float* const* psfs, const int* psf_dims, i
  * Until shapes are set, a handle may run its convolutions in two passes over
  * memory instead of four (volumes up to about 10 million voxels: one
  * workgroup takes a whole (y, z) plane of the spectrum), which needs the
- * kernels' full spectra (4 bytes per voxel, view and kernel kind, allocated
- * on first use; without that memory the four passes run).  The shapes belong
- * to the four passes: mvd_set_tiles selects them, mvd_profile times them, and
- * mvd_default_tiles takes a handle back to its shapes and form at create. */
+ * kernels' full spectra (4 bytes per voxel, view and kernel kind: held from
+ * the second iteration asked for, for a first single one or view-update
+ * during the call only).  The shapes belong to the four passes: mvd_set_tiles
+ * selects them, mvd_profile times them, and mvd_default_tiles takes a handle
+ * back to its shapes and form at create.
+ *
+ * The form depends on the volume's extents and these calls, not on what ran
+ * before: a call from the same estimate gives the same bits each time, and
+ * n calls of one iteration, or of their view-updates in order, give the bits
+ * of one call of n.  The one exception is memory: once an allocation for the
+ * spectra fails, or another one fails and they are given back for it, the
+ * handle takes the four passes, whose results differ from the two-pass form's
+ * in their rounding.  mvd_two_pass_split tells which form a block's last run
+ * took: the split of ny of the two-pass form (>= 1), or 0. */
 int mvd_tile_candidates(int kind, int max_len, int* out, int cap);
 int mvd_tile_shape(int kind, int cfg, int* threads, int* per_tile, int* max_len, int* exact_len);
 int mvd_set_tiles(mvd_handle* h, int cfg_x, int cfg_y, int cfg_z);
 int mvd_get_tiles(const mvd_handle* h, int* cfg);
 int mvd_default_tiles(mvd_handle* h);
+int mvd_two_pass_split(const mvd_handle* h, int block);
 
 /* Schedule of a multi-block handle's runs (the autotuner's other knob).
  * Blocks are independent, so every schedule gives the same results; they

@@ -159,7 +159,7 @@ struct mvd_handle {
   Partial* d_tp_parts = nullptr;
   std::vector<void*> tp_allocs;           // memory of the two-pass form: given back when another
   bool tp_allocating = false;             // allocation fails (tp_release)
-  int64_t role_runs[N_ROLES] = {0, 0, 0, 0};  // iterations asked for per kernel role
+  int64_t tp_asked = 0;                   // iterations asked for in the two-pass form (use_two_pass)
   std::vector<TpJob> tpjobs;              // one per block
   std::vector<TpPass> tp_x, tp_p;         // per block: the x and the plane pass
   bool tp_even = false;                   // equal extents
@@ -252,14 +252,17 @@ struct mvd_handle {
       (void)hipFree(p);
   }
 
-  // Give back the two-pass form's memory (the four passes need none of it);
-  // false if there is none.
+  // Give back the two-pass form's memory (the four passes need none of it;
+  // a later run allocates and builds it again); false if there is none.
   bool tp_release();
 
   void* dalloc(size_t bytes) {
     bytes = (bytes + 255) & ~size_t(255);
     void* p = raw_alloc(bytes);
-    if (!p && !tp_allocating && tp_release()) p = raw_alloc(bytes);
+    if (!p && !tp_allocating && tp_release()) {
+      tp_planned = false;  // the four passes from here on
+      p = raw_alloc(bytes);
+    }
     if (!p)
       throw Error(MVD_ENOMEM, std::string(alloc ? "allocator callback" : "hipMalloc") + " failed for " +
                                   std::to_string(bytes) + " bytes");
@@ -855,9 +858,6 @@ bool mvd_handle::tp_release() {
   for (bool& b : k2_built) b = false;
   d_tp = nullptr;
   d_tp_parts = nullptr;
-  tp_planned = false;
-  if (spec_tp) spec_valid = false;
-  spec_tp = false;
   return true;
 }
 
@@ -1716,14 +1716,22 @@ bool ensure_two_pass(mvd_handle* h, int role) {
   return true;
 }
 
-// Whether a run of n iterations of this role takes the two-pass form.  Its
-// spectra are built once a handle has been asked for a second iteration of a
-// role: for a single one the four passes are done first.
+// Whether a run of n iterations of this role takes the two-pass form.  The
+// handle's plan alone decides, so that a call gives the same bits whatever
+// ran before it.
 bool use_two_pass(mvd_handle* h, int role, int n, bool combined) {
   if (!h->tp_planned || h->tiles_chosen || !(h->tp_even || combined)) return false;
-  const bool again = (h->role_runs[role] += n) >= 2;
-  if (!again && !h->k2_built[role]) return false;
+  h->tp_asked += std::max(n, 1);
   return ensure_two_pass(h, ROLE_P) && ensure_two_pass(h, role);
+}
+
+// A handle asked for a single iteration (or view-update) holds no more
+// memory after it than at create: the two-pass form's is given back, and
+// stays from the second on.  No graph is captured for that first call.
+bool two_pass_once(const mvd_handle* h) { return h->spec_tp && h->tp_asked < 2; }
+
+void finish_run(mvd_handle* h) {
+  if (two_pass_once(h)) (void)h->tp_release();
 }
 
 // One launch of a pass of the two-pass form: blocks [b0, b0 + n), n > 1 only
@@ -2028,7 +2036,7 @@ void prepare_run(mvd_handle* h, int variant, int n, bool classic = false, bool c
 // per run, 102 in the branching graph), other sequences over lanes launch
 // directly.
 bool replay(const mvd_handle* h) {
-  if (!h->use_graphs) return false;
+  if (!h->use_graphs || two_pass_once(h)) return false;
   for (int l : h->block_lane)
     if (l) return false;
   return true;
@@ -2138,7 +2146,7 @@ const std::vector<hipGraphExec_t>& lane_graphs_for(mvd_handle* h, int variant, i
 // Whether the lanes of uneven blocks replay their chains: per-length plans
 // for every pass kind (so that every launch belongs to one lane).
 bool replay_lanes(const mvd_handle* h) {
-  if (!h->use_graphs || replay(h) || h->spec_tp) return false;
+  if (!h->use_graphs || h->spec_tp || replay(h)) return false;
   return h->cfg_x == mvd_exact_cfg(PASS_X) && h->cfg_y == mvd_exact_cfg(PASS_Y) && h->cfg_z == mvd_exact_cfg(PASS_Z);
 }
 
@@ -2167,6 +2175,7 @@ void iterate_impl(mvd_handle* h, int n, int variant) {
   }
   reduce_stats(h, h->stream);
   h->iterations += n;
+  finish_run(h);
 }
 
 void iterate_combined_impl(mvd_handle* h, int n, int variant, int mean) {
@@ -2190,6 +2199,7 @@ void iterate_combined_impl(mvd_handle* h, int n, int variant, int mean) {
   }
   reduce_stats(h, h->stream);
   h->iterations += n;
+  finish_run(h);
 }
 
 // ---- differentiated form -------------------------------------------------
@@ -3091,6 +3101,7 @@ int mvd_view_update(mvd_handle* h, int view, int variant) {
     h->rec_token = 0;
     prepare_run(h, variant, 0);
     enqueue_view(h, h->stream, variant, view);
+    finish_run(h);
   });
 }
 
@@ -3203,6 +3214,11 @@ int mvd_default_tiles(mvd_handle* h) {
     set_tiles(h, pick_cfg(h, PASS_X), pick_cfg(h, PASS_Y), pick_cfg(h, PASS_Z));
     h->tiles_chosen = false;
   });
+}
+
+int mvd_two_pass_split(const mvd_handle* h, int block) {
+  if (!h || block < 0 || block >= (int)h->blocks.size()) return MVD_EINVAL;
+  return h->spec_tp ? h->blocks[block].tpR : 0;
 }
 
 int mvd_set_schedule(mvd_handle* h, int schedule) {

@@ -81,6 +81,7 @@ def lib():
     L.mvd_set_tiles.argtypes = [H, C.c_int, C.c_int, C.c_int]
     L.mvd_get_tiles.argtypes = [H, C.POINTER(C.c_int)]
     L.mvd_default_tiles.argtypes = [H]
+    L.mvd_two_pass_split.argtypes = [H, C.c_int]
     L.mvd_tile_candidates.argtypes = [C.c_int, C.c_int, C.POINTER(C.c_int), C.c_int]
     L.mvd_tile_shape.argtypes = [C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int),
                                  C.POINTER(C.c_int)]
@@ -111,6 +112,7 @@ def lib():
                  "mvd_set_estimate",
                  "mvd_stats", "mvd_synchronize", "mvd_destroy", "mvd_compound_kernel", "mvd_kernel_spectrum",
                  "mvd_view_update", "mvd_profile", "mvd_set_tiles", "mvd_get_tiles", "mvd_default_tiles",
+                 "mvd_two_pass_split",
                  "mvd_tile_candidates", "mvd_tile_shape", "mvd_loss_grad", "mvd_backward", "mvd_set_psfs", "mvd_iterate_noalloc",
                  "mvd_create_blocked", "mvd_blocking", "mvd_set_schedule", "mvd_get_schedule",
                  "mvd_forward_recorded", "mvd_backward_recorded", "mvd_compound_kernel_vjp"):
@@ -448,6 +450,14 @@ class Deconvolver:
         """Back to the launch shapes (and the form of the convolutions) at create."""
         _check(lib().mvd_default_tiles(self._h), self._h)
         return self
+
+    def two_pass_split(self, block=0):
+        """Split of ny of the two-pass convolutions that the block's last run
+        took, 0 where it took the four passes."""
+        n = lib().mvd_two_pass_split(self._h, int(block))
+        if n < 0:
+            raise MVDError(n, "block index out of range")
+        return n
 
     def grid_dims(self, block=0):
         """The computation grid (nx, ny, nz) of a block (larger than the

@@ -23,3 +23,50 @@ def test_lazy_buffers_belong_to_the_handles_stream(mvd):
         segs = [(s["address"], s["total_size"], s["stream"]) for s in torch.cuda.memory_snapshot()]
         for a in new:
             assert [st for lo, n, st in segs if lo <= a < lo + n] == [d.stream.cuda_stream]
+
+
+@pytest.mark.parametrize("dims,variant", [((48, 45, 16), "rl"), ((30, 27, 25), "eff"), ((64, 64, 20), "opt1")])
+@pytest.mark.parametrize("graphs", [False, True])
+def test_bits_do_not_depend_on_what_ran_before(mvd, dims, variant, graphs):
+    """The form of the convolutions comes from the handle's plan alone: the
+    first call gives the bits of a repeated one, single iterations and
+    view-updates those of one longer run."""
+    v, p, w = problem(dims, 2, 810, True)
+
+    def handle():
+        return mvd.Deconvolver(v, p, w, use_graphs=graphs)
+
+    with handle() as d:
+        start = np.full_like(v[0], d.stats()["scale"])
+        first = d.iterate(1, variant).estimate().cpu().numpy()
+        flux = d.stats()["flux"]
+        assert d.two_pass_split() > 0
+        for _ in range(3):
+            d.set_estimate(start).iterate(1, variant)
+            np.testing.assert_array_equal(d.estimate().cpu().numpy(), first)
+            assert d.stats()["flux"] == flux
+        steps = d.iterate(1, variant).iterate(1, variant).estimate().cpu().numpy()
+    with handle() as d:
+        np.testing.assert_array_equal(d.iterate(3, variant).estimate().cpu().numpy(), steps)
+    with handle() as d:
+        for _ in range(3):
+            for k in range(2):
+                d.view_update(k, variant)
+        np.testing.assert_array_equal(d.estimate().cpu().numpy(), steps)
+
+
+def test_one_iteration_leaves_no_memory_behind(mvd):
+    """After a single iteration a handle holds what it held at create (RL:
+    no compound kernel is kept either)."""
+    from tests.test_gpu_failures import CappedAllocator, create
+    v, p, _ = problem((48, 45, 16), 2, 815, False)
+    a = CappedAllocator(mvd, 1 << 40)
+    rc, h = create(mvd, v, p, a)
+    assert rc == mvd.MVD_OK
+    at_create = a.live
+    assert mvd.lib().mvd_iterate(h, 1, 0) == mvd.MVD_OK
+    assert a.live == at_create and mvd.lib().mvd_two_pass_split(h, 0) > 0
+    assert mvd.lib().mvd_iterate(h, 1, 0) == mvd.MVD_OK
+    assert a.live > at_create
+    mvd.lib().mvd_destroy(h)
+    assert a.live == 0
