@@ -116,6 +116,14 @@ typedef void (*mvd_free_fn)(void* ptr, void* ctx);
  *   use_graphs 0 = launch kernels directly, 1 = replay one HIP graph per
  *              iteration (default when options are NULL; handles whose
  *              blocks have different extents replay one per stream lane)
+ *              A caller may capture runs on `stream` into a graph of its own
+ *              (use_graphs 0, and whatever the run builds lazily built by a
+ *              run of the same kind before: two iterations of its variant;
+ *              without those a run of MVD_RL is captured too, and the handle
+ *              keeps to the four passes from then on, see mvd_set_tiles).
+ *              Such a graph may be replayed between the handle's other calls;
+ *              each captured run starts from the estimate at its replay.
+ *              Launch shapes set later need a new capture.
  *   tile_config  0 = autotuned/default pass shapes; k > 0 forces candidate k-1
  *   boundary   MVD_BOUNDARY_CIRCULAR (0): the volume is one period of a
  *              periodic grid (the convolutions wrap around);

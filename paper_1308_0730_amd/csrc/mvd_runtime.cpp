@@ -160,6 +160,7 @@ struct mvd_handle {
   std::vector<void*> tp_allocs;           // memory of the two-pass form: given back when another
   bool tp_allocating = false;             // allocation fails (tp_release)
   int64_t tp_asked = 0;                   // iterations asked for in the two-pass form (use_two_pass)
+  bool caller_graph = false;              // the caller has captured runs on the handle's stream (prepare_run)
   std::vector<TpJob> tpjobs;              // one per block
   std::vector<TpPass> tp_x, tp_p;         // per block: the x and the plane pass
   bool tp_even = false;                   // equal extents
@@ -848,7 +849,7 @@ void drop_graphs(mvd_handle* h) {
 }  // namespace
 
 bool mvd_handle::tp_release() {
-  if (tp_allocs.empty()) return false;
+  if (tp_allocs.empty() || caller_graph) return false;  // the caller's graphs read it
   drop_graphs(this);
   HIPCHECK(hipStreamSynchronize(stream));
   for (void* p : tp_allocs) raw_free(p);
@@ -1719,8 +1720,14 @@ bool ensure_two_pass(mvd_handle* h, int role) {
 // Whether a run of n iterations of this role takes the two-pass form.  The
 // handle's plan alone decides, so that a call gives the same bits whatever
 // ran before it.
-bool use_two_pass(mvd_handle* h, int role, int n, bool combined) {
+bool use_two_pass(mvd_handle* h, int role, int n, bool combined, bool capturing) {
   if (!h->tp_planned || h->tiles_chosen || !(h->tp_even || combined)) return false;
+  if (capturing && !(h->k2_built[ROLE_P] && h->k2_built[role])) {
+    // nothing can be allocated or built now: four passes, from here on, so
+    // that later runs leave the form that the captured ones expect
+    h->tp_planned = false;
+    return false;
+  }
   h->tp_asked += std::max(n, 1);
   return ensure_two_pass(h, ROLE_P) && ensure_two_pass(h, role);
 }
@@ -2009,13 +2016,29 @@ void ensure_combined(mvd_handle* h) {
   if (grown) build_jobs(h);
 }
 
+// Whether the caller is capturing the handle's stream.
+bool capturing(const mvd_handle* h) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(h->stream, &st) == hipSuccess) return st == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
+}
+
 // n: iterations asked for; classic: the launches that the profiler times,
 // never the two-pass form; combined: combined updates follow.
+//
+// A graph that the caller captures replays between the handle's own calls,
+// unseen by it: from then on every run, captured or not, starts from psi
+// itself and not from the spectrum that the last one left, and the two-pass
+// form's memory stays where it is.
 void prepare_run(mvd_handle* h, int variant, int n, bool classic = false, bool combined = false) {
   if (variant < MVD_RL || variant > MVD_OPT2) bad("variant must be MVD_RL, MVD_EFF, MVD_OPT1 or MVD_OPT2");
   const int role = variant == MVD_RL ? ROLE_P : variant;
   ensure_role(h, role);
-  const bool two = !classic && use_two_pass(h, role, n, combined);
+  const bool cap = capturing(h);
+  h->caller_graph |= cap;
+  if (h->caller_graph) h->spec_valid = false;
+  const bool two = !classic && use_two_pass(h, role, n, combined, cap);
   h->stat_grid = two ? h->tp_tiles : h->grid_x;
   h->stat_parts = two ? h->d_tp_parts : h->d_parts;
   if ((!h->spec_valid || h->spec_tp != two) && !h->blocked) {
@@ -2639,6 +2662,8 @@ void set_psfs_impl(mvd_handle* h, const float* const* psfs, const int* psf_dims,
   for (int r = 1; r < N_ROLES; ++r) h->built[r] = false;
   for (bool& k : h->k2_built) k = false;
   build_jobs(h);
+  // the caller's graphs see new PSFs at once, as those of the four passes do
+  if (h->caller_graph && B.K2[ROLE_P]) (void)ensure_two_pass(h, ROLE_P);
 }
 
 // Limit every voxel's summed weight to the overlap number of its block (see

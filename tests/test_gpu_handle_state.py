@@ -70,3 +70,83 @@ def test_one_iteration_leaves_no_memory_behind(mvd):
     assert a.live > at_create
     mvd.lib().mvd_destroy(h)
     assert a.live == 0
+
+
+@pytest.mark.parametrize("warm", [0, 1, 2])
+@pytest.mark.parametrize("dims", [(48, 45, 16), (64, 300, 300)])
+def test_runs_captured_by_the_caller(mvd, warm, dims):
+    """A caller's graph of a run, captured on a handle that has run nothing,
+    one iteration or two, replayed between eager runs, the profiler, new
+    estimates and new PSFs, gives what an eager handle of the same form
+    gives.  (64, 300, 300) has four passes only."""
+    import torch
+    v, p, _ = problem(dims, 2, 830, False)
+    q = [x[:, ::-1].copy() for x in p]
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        d, e = (mvd.Deconvolver(v, p, use_graphs=False) for _ in range(2))
+        start = np.full_like(v[0], d.stats()["scale"])
+        if warm:
+            d.iterate(warm, "rl").set_estimate(start)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        d.iterate(2, "rl")
+    with torch.cuda.stream(s):
+        form = d.two_pass_split() > 0
+        assert form == (warm == 2 and dims[1] < 300)
+        if not form:
+            e.set_tiles(*e.tiles())
+
+        def same():
+            np.testing.assert_array_equal(d.estimate().cpu().numpy(), e.estimate().cpu().numpy())
+            assert d.stats()["flux"] == e.stats()["flux"]
+
+        def replay():
+            g.replay()
+            e.iterate(2, "rl")
+            same()
+
+        replay()
+        replay()
+        for x in (d, e):
+            x.iterate(1, "rl")
+        replay()
+        for x in (d, e):
+            x.profile(1, "rl")
+            x.view_update(1, "rl")
+        replay()
+        for x in (d, e):
+            x.set_estimate(start)
+        replay()
+        for x in (d, e):
+            x.set_psfs(q)
+        replay()
+        d.close()
+        e.close()
+
+
+def test_captured_runs_keep_their_memory(mvd):
+    """After a capture the two-pass form's memory is not given back when
+    another allocation fails: the graph still reads it."""
+    import ctypes as C
+    import torch
+    from tests.test_gpu_failures import CappedAllocator
+    v, p, _ = problem((48, 45, 16), 2, 840, False)
+    L, s, a = mvd.lib(), torch.cuda.Stream(), CappedAllocator(mvd, 1 << 40)
+    m, h, out = mvd._Marshalled(v, p, None, torch.device("cuda"), False), C.c_void_p(), np.empty_like(v[0])
+    with torch.cuda.stream(s):
+        opts = a.options(mvd)
+        opts.use_graphs = 0
+        assert L.mvd_create(C.byref(h), C.byref(m.problem), C.byref(opts)) == mvd.MVD_OK
+        assert L.mvd_iterate(h, 2, 0) == mvd.MVD_OK
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        assert L.mvd_iterate(h, 1, 0) == mvd.MVD_OK
+    with torch.cuda.stream(s), mvd.Deconvolver(v, p) as e:
+        live = a.cap = a.live
+        assert L.mvd_iterate(h, 1, 2) == mvd.MVD_ENOMEM and a.live == live
+        g.replay()
+        assert L.mvd_get_estimate(h, out.ctypes.data, mvd.MEM_HOST, 0) == mvd.MVD_OK
+        np.testing.assert_array_equal(out, e.iterate(3, "rl").estimate().cpu().numpy())
+        L.mvd_destroy(h)
+    assert a.live == 0
