@@ -139,21 +139,22 @@ struct mvd_handle {
   std::vector<int> order[3];
   std::vector<Group> groups[3];
   // per pass kind and block: the one-block group of that block in the
-  // sorted job order (the block-major schedules), set with the per-length
-  // plans of all three kinds
+  // sorted job order (launches over one block: the block-major schedules,
+  // blocks without a two-pass form beside blocks that have one, combined
+  // updates of uneven blocks)
   std::vector<Group> bgroups[3];
   // two-pass convolutions (mvd_two_pass.h): planned at create, used until
   // launch shapes are set; one launch covers every block of a pass where the
-  // blocks have equal extents, else one block (on its lane; combined updates
-  // only: the sequential runs of uneven blocks let the lanes run apart for a
-  // whole iteration instead)
+  // blocks have equal extents, else one block, on its lane.  Uneven blocks
+  // choose each for itself: one without a two-pass form takes four passes in
+  // the same chain.
   struct TpPass {
-    int grid = 0;     // tiles of the block
+    int grid = 0;     // tiles of the block (x: the four-pass ones where it has no two-pass form)
     int threads = 0;
     size_t lds = 0;
     int off = 0;      // x tiles of the blocks before it
   };
-  bool tp_planned = false;
+  bool tp_planned = false;                // some block has the form
   bool tiles_chosen = false;  // launch shapes were set (mvd_set_tiles): four-pass
   TpJob* d_tp = nullptr;                  // allocated, with the rest, on first use (ensure_two_pass)
   Partial* d_tp_parts = nullptr;
@@ -173,9 +174,10 @@ struct mvd_handle {
   // two-pass form, and n)
   int schedule = 0;
   std::map<std::pair<int, int>, hipGraphExec_t> run_exec;
-  // blocks on several lanes: one chain per lane (key: variant and n of a
-  // block-major run, n = 0 for a pass-major iteration)
+  // blocks on several lanes: one chain per lane that has blocks (key: form,
+  // scheme and variant as in exec, and the iterations in the chain)
   std::map<std::pair<int, int>, std::vector<hipGraphExec_t>> lane_exec;
+  std::vector<int> lanes;                 // the lanes that have blocks
   FftPlan* d_plans = nullptr;
   float2* d_tw = nullptr;
   Partial* d_parts = nullptr;
@@ -810,6 +812,9 @@ void build_jobs(mvd_handle* h) {
       load[best] += g.first;
     }
   }
+  h->lanes.clear();
+  for (int l = 0; l <= h->nside; ++l)
+    if (std::find(h->block_lane.begin(), h->block_lane.end(), l) != h->block_lane.end()) h->lanes.push_back(l);
   for (int k = 0; k < 3; ++k) {
     auto& ord = h->order[k];
     ord.resize(h->jobs.size());
@@ -924,15 +929,13 @@ void set_tiles(mvd_handle* h, int cx, int cy, int cz) {
     g[k] = (int)tiles;
   }
   for (int k = 0; k < 3; ++k) {
-    h->bgroups[k].clear();
-    if (c[k] != mvd_exact_cfg(k)) continue;
-    h->bgroups[k].resize(h->blocks.size());
+    h->bgroups[k].assign(h->blocks.size(), {});
     int64_t off = 0;
     const auto& ord = h->order[k];
     for (size_t i = 0; i < ord.size(); ++i) {
       const int b = ord[i];
       const int len = job_len(h->blocks[b], k);
-      const int t = mvd_tiles(h->jobs[b], k, mvd_exact_param(k, len));
+      const int t = mvd_tiles(h->jobs[b], k, c[k] == mvd_exact_cfg(k) ? mvd_exact_param(k, len) : mvd_cfg_param(k, c[k]));
       h->bgroups[k][b] = mvd_handle::Group{len, (int)i, 1, t, (int)off, h->block_lane[b], -1};
       off += t;
     }
@@ -1045,8 +1048,8 @@ constexpr int kTpSplits[] = {1, 2, 3, 4, 5, 6, 8, 9};
 size_t tp_plane_lds(int n1, int nz) { return ((size_t)nz * (n1 | 1) + nz + n1) * sizeof(float2); }
 
 // Split R of ny = R n1 for the two-pass form of a block, 0 if it has none.
-// A function of the block's own extents, so that a block gives the same
-// bits alone and in a batch.
+// A function of the block's own extents, so that a block with the form gives
+// the same bits alone and in any batch.
 //
 // Up to 5 Mi spectrum values the form is the faster one (three views, four
 // iterations, weights; four-pass against two-pass: 64^3 615 / 503 us, 128^3
@@ -1191,20 +1194,28 @@ bool tp_plan_block(mvd_handle* h, const Block& B, const std::vector<FftPlan>& pl
 void tp_plan(mvd_handle* h, const std::vector<FftPlan>& plans) {
   const int nb = (int)h->blocks.size();
   const Block& B = h->blocks[0];
+  bool any = false;
   h->tp_even = true;
   for (const auto& X : h->blocks) h->tp_even &= X.nx == B.nx && X.ny == B.ny && X.nz == B.nz;
+  if (h->linear && !h->tp_even) return;  // these give the bits of the per-length four-pass plans
   h->tpjobs.assign(nb, TpJob{});
   h->tp_x.resize(nb), h->tp_p.resize(nb);
   int64_t xt = 0, pt = 0;
   for (int b = 0; b < nb; ++b) {
-    if (!tp_plan_block(h, h->blocks[b], plans, h->tp_even ? nb : 1, h->tpjobs[b], h->tp_x[b], h->tp_p[b])) return;
+    if (tp_plan_block(h, h->blocks[b], plans, h->tp_even ? nb : 1, h->tpjobs[b], h->tp_x[b], h->tp_p[b])) {
+      any = true;
+    } else {
+      h->blocks[b].tpR = 0;
+      h->tpjobs[b] = TpJob{};
+      h->tp_x[b] = {h->bgroups[PASS_X][b].grid, 0, 0, 0};
+    }
     h->tp_x[b].off = (int)xt;
     xt += h->tp_x[b].grid;
     pt += (int64_t)h->tp_p[b].grid * h->nviews;
     if (xt > 0x7fffffff || pt > 0x7fffffff) return;
   }
   h->tp_tiles = (int)xt;
-  h->tp_planned = true;
+  h->tp_planned = any;
 }
 
 // Refresh the pointers of the two-pass jobs (buffers come and go).
@@ -1697,7 +1708,7 @@ bool ensure_two_pass(mvd_handle* h, int role) {
       h->d_tp = (TpJob*)h->dalloc(h->tpjobs.size() * sizeof(TpJob));
     }
     for (auto& B : h->blocks)
-      if (!B.K2[role])
+      if (B.tpR && !B.K2[role])
         B.K2[role] = (float*)h->dalloc((size_t)h->nviews * (B.M + 1) * B.ny * B.nz * sizeof(float2));
   } catch (const Error&) {
     ok = false;
@@ -1710,6 +1721,7 @@ bool ensure_two_pass(mvd_handle* h, int role) {
   }
   tp_upload(h);
   for (size_t b = 0; b < nb; ++b) {
+    if (!h->blocks[b].tpR) continue;
     const TpArgs a{h->d_tp + b, 1, h->d_tw, h->stream, h->tp_p[b].grid * h->nviews};
     HIPCHECK(mvd_launch_plane_kernel(a, h->tp_p[b].lds, role, h->blocks[b].K2[role]));
   }
@@ -1720,8 +1732,8 @@ bool ensure_two_pass(mvd_handle* h, int role) {
 // Whether a run of n iterations of this role takes the two-pass form.  The
 // handle's plan alone decides, so that a call gives the same bits whatever
 // ran before it.
-bool use_two_pass(mvd_handle* h, int role, int n, bool combined, bool capturing) {
-  if (!h->tp_planned || h->tiles_chosen || !(h->tp_even || combined)) return false;
+bool use_two_pass(mvd_handle* h, int role, int n, bool capturing) {
+  if (!h->tp_planned || h->tiles_chosen) return false;
   if (capturing && !(h->k2_built[ROLE_P] && h->k2_built[role])) {
     // nothing can be allocated or built now: four passes, from here on, so
     // that later runs leave the form that the captured ones expect
@@ -1754,29 +1766,6 @@ void tp_launch_plane(mvd_handle* h, hipStream_t s, int b0, int n, int v, int rol
   const auto& p = h->tp_p[b0];
   const TpArgs a{h->d_tp + b0, n, h->d_tw, s, n * p.grid};
   HIPCHECK(mvd_launch_plane(a, p.threads, p.lds, v, role, conj, src_saved));
-}
-// A pass over every block: f(stream, first block, blocks), forked over the
-// lanes and joined for uneven blocks (see run_groups).
-template <class F>
-void tp_all(mvd_handle* h, hipStream_t s, F&& f) {
-  const int nb = (int)h->blocks.size();
-  if (h->tp_even) {
-    f(s, 0, nb);
-    return;
-  }
-  HIPCHECK(hipEventRecord(h->ev_fork, s));
-  for (int l = 0; l < h->nside; ++l) HIPCHECK(hipStreamWaitEvent(h->side[l], h->ev_fork, 0));
-  for (int b = 0; b < nb; ++b) f(h->block_lane[b] ? h->side[h->block_lane[b] - 1] : s, b, 1);
-  for (int l = 0; l < h->nside; ++l) {
-    HIPCHECK(hipEventRecord(h->ev_join[l], h->side[l]));
-    HIPCHECK(hipStreamWaitEvent(s, h->ev_join[l], 0));
-  }
-}
-void tp_x(mvd_handle* h, hipStream_t s, int mode, int v, int opt) {
-  tp_all(h, s, [&](hipStream_t st, int b0, int n) { tp_launch_x(h, st, b0, n, mode, v, opt); });
-}
-void tp_plane(mvd_handle* h, hipStream_t s, int v, int role, int conj, int src_saved) {
-  tp_all(h, s, [&](hipStream_t st, int b0, int n) { tp_launch_plane(h, st, b0, n, v, role, conj, src_saved); });
 }
 // A view-update of blocks of equal extents.
 void tp_view(mvd_handle* h, hipStream_t s, int b0, int n, int v, int role, int conj_back) {
@@ -1813,7 +1802,7 @@ struct PassTimer {
 void enqueue_view_passes(mvd_handle* h, hipStream_t s, int variant, int v, PassTimer* t, bool spec_out) {
   const int role = variant == MVD_RL ? ROLE_P : variant;
   const int conj_back = variant == MVD_RL ? 1 : 0;
-  if (h->spec_tp && !t) {
+  if (h->spec_tp && !t) {  // blocks of equal extents
     tp_view(h, s, 0, (int)h->blocks.size(), v, role, conj_back);
     return;
   }
@@ -1880,43 +1869,59 @@ void enqueue_iteration(mvd_handle* h, hipStream_t s, int variant, PassTimer* t =
   }
 }
 
-// One view-update of block b alone on stream s (the block-major schedules):
-// every pass launches the per-length plan over that block only.
+// One pass over block b alone on stream s, with the handle's launch shape.
+void block_x(mvd_handle* h, hipStream_t s, int b, int mode, int v, Partial* parts, int opt) {
+  const auto& g = h->bgroups[PASS_X][b];
+  const LaunchArgs a = group_args(h, s, PASS_X, g);
+  HIPCHECK(h->cfg_x == mvd_exact_cfg(PASS_X) ? mvd_launch_x_exact(a, g.len, mode, v, parts, h->d_flags, opt)
+                                             : mvd_launch_x(a, h->cfg_x, mode, v, parts, h->d_flags, opt));
+}
+void block_y(mvd_handle* h, hipStream_t s, int b, int inv, int v) {
+  const auto& g = h->bgroups[PASS_Y][b];
+  const LaunchArgs a = group_args(h, s, PASS_Y, g);
+  HIPCHECK(h->cfg_y == mvd_exact_cfg(PASS_Y) ? mvd_launch_y_exact(a, g.len, inv, v)
+                                             : mvd_launch_y(a, h->cfg_y, inv, v));
+}
+void block_z(mvd_handle* h, hipStream_t s, int b, int v, int role, int conjH, int src_saved) {
+  const auto& g = h->bgroups[PASS_Z][b];
+  const LaunchArgs a = group_args(h, s, PASS_Z, g);
+  HIPCHECK(h->cfg_z == mvd_exact_cfg(PASS_Z) ? mvd_launch_z_exact(a, g.len, v, role, conjH, src_saved)
+                                             : mvd_launch_z(a, h->cfg_z, v, role, conjH, src_saved));
+}
+// Partial results of a four-pass block's x passes.
+Partial* block_parts(mvd_handle* h, int b, int v) {
+  return h->spec_tp ? h->d_tp_parts + (size_t)v * h->tp_tiles + h->tp_x[b].off
+                    : h->d_parts + (size_t)v * h->grid_x + h->bgroups[PASS_X][b].part_off;
+}
+
+bool two_pass(const mvd_handle* h, int b) { return h->spec_tp && h->blocks[b].tpR; }
+
+// One view-update of block b alone on stream s, in the block's own form.
 void enqueue_view_block(mvd_handle* h, hipStream_t s, int variant, int v, int b) {
   const int role = variant == MVD_RL ? ROLE_P : variant;
   const int conj_back = variant == MVD_RL ? 1 : 0;
-  if (h->spec_tp) {
+  if (two_pass(h, b)) {
     tp_view(h, s, b, 1, v, role, conj_back);
     return;
   }
-  Partial* parts = h->d_parts + (size_t)v * h->grid_x;
-  const auto& gx = h->bgroups[PASS_X][b];
-  const auto& gy = h->bgroups[PASS_Y][b];
-  const auto& gz = h->bgroups[PASS_Z][b];
-  auto y = [&](int inv) { HIPCHECK(mvd_launch_y_exact(group_args(h, s, PASS_Y, gy), gy.len, inv, v)); };
-  auto z = [&](int r, int cj) {
-    HIPCHECK(mvd_launch_z_exact(group_args(h, s, PASS_Z, gz), gz.len, v, r, cj, 0));
-  };
-  auto x = [&](int mode) {
-    HIPCHECK(mvd_launch_x_exact(group_args(h, s, PASS_X, gx), gx.len, mode, v, parts + gx.part_off, h->d_flags,
-                                XOPT_SPEC));
-  };
-  y(0);
-  z(ROLE_P, 0);
-  y(1);
-  x(1);
-  y(0);
-  z(role, conj_back);
-  y(1);
-  x(2);
+  Partial* parts = block_parts(h, b, v);
+  block_y(h, s, b, 0, v);
+  block_z(h, s, b, v, ROLE_P, 0, 0);
+  block_y(h, s, b, 1, v);
+  block_x(h, s, b, 1, v, parts, XOPT_SPEC);
+  block_y(h, s, b, 0, v);
+  block_z(h, s, b, v, role, conj_back, 0);
+  block_y(h, s, b, 1, v);
+  block_x(h, s, b, 2, v, parts, XOPT_SPEC);
+}
+
+bool per_length_plans(const mvd_handle* h) {
+  return h->cfg_x == mvd_exact_cfg(PASS_X) && h->cfg_y == mvd_exact_cfg(PASS_Y) && h->cfg_z == mvd_exact_cfg(PASS_Z);
 }
 
 bool block_major(const mvd_handle* h) {
   if (h->schedule == MVD_SCHEDULE_PASS_MAJOR || h->blocks.size() < 2 || h->blocked || h->no_alloc) return false;
-  if (h->spec_tp) return true;
-  for (int k = 0; k < 3; ++k)
-    if (h->bgroups[k].size() != h->blocks.size()) return false;
-  return true;
+  return h->spec_tp || per_length_plans(h);
 }
 
 // n iterations with a block-major schedule: every lane's stream takes its
@@ -1941,20 +1946,71 @@ void enqueue_lane_blocks(mvd_handle* h, hipStream_t s, int variant, int n, int l
   }
 }
 
-// f(lane, its stream) for every lane, forked from s and joined back.
+// f(lane, its stream) for every lane that has blocks, forked from s and
+// joined back.
 template <class F>
 void over_lanes(mvd_handle* h, hipStream_t s, F&& f) {
-  HIPCHECK(hipEventRecord(h->ev_fork, s));
-  for (int l = 0; l < h->nside; ++l) HIPCHECK(hipStreamWaitEvent(h->side[l], h->ev_fork, 0));
-  for (int l = 0; l <= h->nside; ++l) f(l, l ? h->side[l - 1] : s);
-  for (int l = 0; l < h->nside; ++l) {
-    HIPCHECK(hipEventRecord(h->ev_join[l], h->side[l]));
-    HIPCHECK(hipStreamWaitEvent(s, h->ev_join[l], 0));
+  if (h->lanes.back()) HIPCHECK(hipEventRecord(h->ev_fork, s));
+  for (int l : h->lanes)
+    if (l) HIPCHECK(hipStreamWaitEvent(h->side[l - 1], h->ev_fork, 0));
+  for (int l : h->lanes) f(l, l ? h->side[l - 1] : s);
+  for (int l : h->lanes)
+    if (l) {
+      HIPCHECK(hipEventRecord(h->ev_join[l - 1], h->side[l - 1]));
+      HIPCHECK(hipStreamWaitEvent(s, h->ev_join[l - 1], 0));
+    }
+}
+// f(block, its lane's stream) for every block
+template <class F>
+void over_blocks(mvd_handle* h, hipStream_t s, F&& f) {
+  over_lanes(h, s, [&](int l, hipStream_t sl) {
+    for (int b = 0; b < (int)h->blocks.size(); ++b)
+      if (h->block_lane[b] == l) f(b, sl);
+  });
+}
+
+// A combined update of blocks [b0, b0 + n) of equal extents in the two-pass
+// form (see enqueue_combined_iteration).
+void tp_combined(mvd_handle* h, hipStream_t s, int b0, int n, int role, int conj_back, bool geo) {
+  const int N = h->nviews;
+  // the saved spectrum is the x passes': every view's plane pass reads it
+  for (int b = b0; b < b0 + n; ++b) {
+    const Block& B = h->blocks[b];
+    HIPCHECK(hipMemcpyAsync(B.saved, B.spec, (size_t)(B.M + 1) * B.ny * B.nz * sizeof(float2),
+                            hipMemcpyDeviceToDevice, s));
+  }
+  for (int v = 0; v < N; ++v) {
+    const int opt = (v == 0 ? XOPT_FIRST : 0) | (geo ? XOPT_GEO : 0);
+    tp_launch_plane(h, s, b0, n, v, ROLE_P, 0, 1);
+    tp_launch_x(h, s, b0, n, 1, v, XOPT_SPEC);
+    tp_launch_plane(h, s, b0, n, v, role, conj_back, 0);
+    tp_launch_x(h, s, b0, n, v < N - 1 ? 3 : 4, v, opt | XOPT_SPEC);
   }
 }
 
-void enqueue_run_blocks(mvd_handle* h, hipStream_t s, int variant, int n) {
-  over_lanes(h, s, [&](int l, hipStream_t sl) { enqueue_lane_blocks(h, sl, variant, n, l); });
+// A combined update of block b alone on stream s, in the block's own form.
+void enqueue_combined_block(mvd_handle* h, hipStream_t s, int variant, bool geo, int b) {
+  const int role = variant == MVD_RL ? ROLE_P : variant;
+  const int conj_back = variant == MVD_RL ? 1 : 0;
+  const int N = h->nviews;
+  if (two_pass(h, b)) {
+    tp_combined(h, s, b, 1, role, conj_back, geo);
+    return;
+  }
+  const Block& B = h->blocks[b];
+  block_y(h, s, b, 0, 0);
+  HIPCHECK(hipMemcpyAsync(B.saved, B.spec, B.spec_elems * 2 * sizeof(float), hipMemcpyDeviceToDevice, s));
+  for (int v = 0; v < N; ++v) {
+    const int opt = (v == 0 ? XOPT_FIRST : 0) | (geo ? XOPT_GEO : 0);
+    Partial* parts = block_parts(h, b, v);
+    block_z(h, s, b, v, ROLE_P, 0, 1);
+    block_y(h, s, b, 1, v);
+    block_x(h, s, b, 1, v, parts, XOPT_SPEC);
+    block_y(h, s, b, 0, v);
+    block_z(h, s, b, v, role, conj_back, 0);
+    block_y(h, s, b, 1, v);
+    block_x(h, s, b, v < N - 1 ? 3 : 4, v, parts, v < N - 1 ? opt : opt | XOPT_SPEC);
+  }
 }
 
 // One combined update (eq. 51): every view's back-projected ratio is taken
@@ -1967,18 +2023,8 @@ void enqueue_combined_iteration(mvd_handle* h, hipStream_t s, int variant, bool 
   const int role = variant == MVD_RL ? ROLE_P : variant;
   const int conj_back = variant == MVD_RL ? 1 : 0;
   const int N = h->nviews;
-  if (h->spec_tp) {
-    // the saved spectrum is the x passes': every view's plane pass reads it
-    for (const auto& B : h->blocks)
-      HIPCHECK(hipMemcpyAsync(B.saved, B.spec, (size_t)(B.M + 1) * B.ny * B.nz * sizeof(float2),
-                              hipMemcpyDeviceToDevice, s));
-    for (int v = 0; v < N; ++v) {
-      const int opt = (v == 0 ? XOPT_FIRST : 0) | (geo ? XOPT_GEO : 0);
-      tp_plane(h, s, v, ROLE_P, 0, 1);
-      tp_x(h, s, 1, v, XOPT_SPEC);
-      tp_plane(h, s, v, role, conj_back, 0);
-      tp_x(h, s, v < N - 1 ? 3 : 4, v, opt | XOPT_SPEC);
-    }
+  if (h->spec_tp) {  // blocks of equal extents
+    tp_combined(h, s, 0, (int)h->blocks.size(), role, conj_back, geo);
     return;
   }
   run_y(h, s, 0, 0);
@@ -2025,25 +2071,32 @@ bool capturing(const mvd_handle* h) {
 }
 
 // n: iterations asked for; classic: the launches that the profiler times,
-// never the two-pass form; combined: combined updates follow.
+// never the two-pass form.
 //
 // A graph that the caller captures replays between the handle's own calls,
 // unseen by it: from then on every run, captured or not, starts from psi
 // itself and not from the spectrum that the last one left, and the two-pass
 // form's memory stays where it is.
-void prepare_run(mvd_handle* h, int variant, int n, bool classic = false, bool combined = false) {
+void prepare_run(mvd_handle* h, int variant, int n, bool classic = false) {
   if (variant < MVD_RL || variant > MVD_OPT2) bad("variant must be MVD_RL, MVD_EFF, MVD_OPT1 or MVD_OPT2");
   const int role = variant == MVD_RL ? ROLE_P : variant;
   ensure_role(h, role);
   const bool cap = capturing(h);
   h->caller_graph |= cap;
   if (h->caller_graph) h->spec_valid = false;
-  const bool two = !classic && use_two_pass(h, role, n, combined, cap);
+  const bool two = !classic && use_two_pass(h, role, n, cap);
   h->stat_grid = two ? h->tp_tiles : h->grid_x;
   h->stat_parts = two ? h->d_tp_parts : h->d_parts;
   if ((!h->spec_valid || h->spec_tp != two) && !h->blocked) {
-    if (two)
-      tp_x(h, h->stream, 0, 0, XOPT_SPEC);
+    if (two && h->tp_even)
+      tp_launch_x(h, h->stream, 0, (int)h->blocks.size(), 0, 0, XOPT_SPEC);
+    else if (two)
+      over_blocks(h, h->stream, [&](int b, hipStream_t s) {
+        if (h->blocks[b].tpR)
+          tp_launch_x(h, s, b, 1, 0, 0, XOPT_SPEC);
+        else
+          block_x(h, s, b, 0, 0, nullptr, XOPT_SPEC);
+      });
     else
       run_x(h, h->stream, 0, 0, nullptr, XOPT_SPEC);
     h->spec_valid = true;
@@ -2055,15 +2108,8 @@ void prepare_run(mvd_handle* h, int variant, int n, bool classic = false, bool c
 // that the graph is a chain.  A graph whose branches are the lanes of
 // uneven blocks has ended the process inside its replay (a host segmentation
 // fault, now and then, at hundreds of replays).  The lanes of uneven blocks
-// replay a chain each (lane_graphs_for; 48 blocks launched directly instead: 113 ms
-// per run, 102 in the branching graph), other sequences over lanes launch
-// directly.
-bool replay(const mvd_handle* h) {
-  if (!h->use_graphs || two_pass_once(h)) return false;
-  for (int l : h->block_lane)
-    if (l) return false;
-  return true;
-}
+// replay a chain each instead (run_lanes).
+bool replay(const mvd_handle* h) { return h->use_graphs && h->lanes.size() == 1 && !two_pass_once(h); }
 
 // scheme 0: sequential; 1, 2: combined with the geometric / arithmetic mean
 hipGraphExec_t graph_for(mvd_handle* h, int variant, int scheme = 0) {
@@ -2104,7 +2150,7 @@ hipGraphExec_t run_graph_for(mvd_handle* h, int variant, int n) {
   hipGraph_t g = nullptr;
   HIPCHECK(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
   try {
-    enqueue_run_blocks(h, h->cap, variant, n);
+    enqueue_lane_blocks(h, h->cap, variant, n, 0);
   } catch (...) {
     (void)hipStreamEndCapture(h->cap, &g);
     if (g) (void)hipGraphDestroy(g);
@@ -2126,51 +2172,57 @@ hipGraphExec_t run_graph_for(mvd_handle* h, int variant, int n) {
   return ex;
 }
 
-// The chains of the lanes of uneven blocks: each lane's part of a block-major
-// run of n iterations, or (n = 0) of a pass-major iteration, as a graph of
-// its own that is launched on the lane's stream.
-const std::vector<hipGraphExec_t>& lane_graphs_for(mvd_handle* h, int variant, int n) {
-  const auto key = std::make_pair(variant, n);
-  auto it = h->lane_exec.find(key);
-  if (it != h->lane_exec.end()) return it->second;
-  if (h->lane_exec.size() >= 4) drop_graphs(h);  // bounded, as the graphs of whole runs
-  std::vector<hipGraphExec_t> ex;
-  try {
-    for (int l = 0; l <= h->nside; ++l) {
-      hipGraph_t g = nullptr;
-      HIPCHECK(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
-      h->only_lane = l;
-      try {
-        if (n)
-          enqueue_lane_blocks(h, h->cap, variant, n, l);
-        else
-          for (int v = 0; v < h->nviews; ++v) enqueue_view(h, h->cap, variant, v, nullptr);
-      } catch (...) {
-        h->only_lane = -1;
-        (void)hipStreamEndCapture(h->cap, &g);
-        if (g) (void)hipGraphDestroy(g);
-        throw;
-      }
-      h->only_lane = -1;
-      HIPCHECK(hipStreamEndCapture(h->cap, &g));
-      hipGraphExec_t e = nullptr;
-      const hipError_t rc = hipGraphInstantiate(&e, g, nullptr, nullptr, 0);
-      (void)hipGraphDestroy(g);
-      HIPCHECK(rc);
-      ex.push_back(e);
-    }
-  } catch (...) {
-    for (auto e : ex) (void)hipGraphExecDestroy(e);
-    throw;
+// A sequence of uneven blocks, reps times: f(lane, stream) enqueues a lane's
+// part of it, every launch of which belongs to that lane.  Blocks are
+// independent, so the lanes run apart until the end.  With graphs each lane
+// replays its part as a graph of its own on its stream (key: see lane_exec).
+template <class F>
+void run_lanes(mvd_handle* h, std::pair<int, int> key, int reps, F&& f) {
+  if (!h->use_graphs || two_pass_once(h)) {
+    over_lanes(h, h->stream, [&](int l, hipStream_t s) {
+      for (int i = 0; i < reps; ++i) f(l, s);
+    });
+    return;
   }
-  return h->lane_exec[key] = ex;
+  auto it = h->lane_exec.find(key);
+  if (it == h->lane_exec.end()) {
+    if (h->lane_exec.size() >= 4) drop_graphs(h);  // bounded, as the graphs of whole runs
+    std::vector<hipGraphExec_t> ex;
+    try {
+      for (int l : h->lanes) {
+        hipGraph_t g = nullptr;
+        HIPCHECK(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
+        try {
+          f(l, h->cap);
+        } catch (...) {
+          (void)hipStreamEndCapture(h->cap, &g);
+          if (g) (void)hipGraphDestroy(g);
+          throw;
+        }
+        HIPCHECK(hipStreamEndCapture(h->cap, &g));
+        hipGraphExec_t e = nullptr;
+        const hipError_t rc = hipGraphInstantiate(&e, g, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(g);
+        HIPCHECK(rc);
+        ex.push_back(e);
+      }
+    } catch (...) {
+      for (auto e : ex) (void)hipGraphExecDestroy(e);
+      throw;
+    }
+    it = h->lane_exec.emplace(key, std::move(ex)).first;
+  }
+  size_t k = 0;
+  over_lanes(h, h->stream, [&](int, hipStream_t s) {
+    for (int i = 0; i < reps; ++i) HIPCHECK(hipGraphLaunch(it->second[k], s));
+    ++k;
+  });
 }
 
-// Whether the lanes of uneven blocks replay their chains: per-length plans
-// for every pass kind (so that every launch belongs to one lane).
-bool replay_lanes(const mvd_handle* h) {
-  if (!h->use_graphs || h->spec_tp || replay(h)) return false;
-  return h->cfg_x == mvd_exact_cfg(PASS_X) && h->cfg_y == mvd_exact_cfg(PASS_Y) && h->cfg_z == mvd_exact_cfg(PASS_Z);
+// Key of lane_exec: form, scheme (0 sequential, 1 and 2 combined as in
+// graph_for) and variant; n iterations in the chain.
+std::pair<int, int> lane_key(const mvd_handle* h, int scheme, int variant, int n) {
+  return {(h->spec_tp ? 12 : 0) + scheme * 4 + variant, n};
 }
 
 void iterate_impl(mvd_handle* h, int n, int variant) {
@@ -2179,17 +2231,30 @@ void iterate_impl(mvd_handle* h, int n, int variant) {
   if (n == 0) return;
   h->rec_token = 0;
   prepare_run(h, variant, n);
-  if (replay_lanes(h)) {
-    const bool major = block_major(h);
-    const auto& ex = lane_graphs_for(h, variant, major ? n : 0);
-    over_lanes(h, h->stream, [&](int l, hipStream_t sl) {
-      for (int i = 0; i < (major ? 1 : n); ++i) HIPCHECK(hipGraphLaunch(ex[l], sl));
+  const bool uneven = h->lanes.size() > 1;
+  if (uneven && block_major(h)) {
+    run_lanes(h, lane_key(h, 0, variant, n), 1,
+              [&](int l, hipStream_t s) { enqueue_lane_blocks(h, s, variant, n, l); });
+  } else if (uneven && h->spec_tp) {
+    run_lanes(h, lane_key(h, 0, variant, 1), n,
+              [&](int l, hipStream_t s) { enqueue_lane_blocks(h, s, variant, 1, l); });
+  } else if (uneven && h->use_graphs && per_length_plans(h)) {
+    // pass-major: a pass of a lane launches all its blocks
+    run_lanes(h, lane_key(h, 0, variant, 1), n, [&](int l, hipStream_t s) {
+      h->only_lane = l;
+      try {
+        for (int v = 0; v < h->nviews; ++v) enqueue_view(h, s, variant, v, nullptr);
+      } catch (...) {
+        h->only_lane = -1;
+        throw;
+      }
+      h->only_lane = -1;
     });
   } else if (block_major(h)) {
     if (replay(h))
       HIPCHECK(hipGraphLaunch(run_graph_for(h, variant, n), h->stream));
     else
-      enqueue_run_blocks(h, h->stream, variant, n);
+      enqueue_lane_blocks(h, h->stream, variant, n, 0);
   } else if (replay(h)) {
     hipGraphExec_t ex = graph_for(h, variant);
     for (int i = 0; i < n; ++i) HIPCHECK(hipGraphLaunch(ex, h->stream));
@@ -2212,9 +2277,14 @@ void iterate_combined_impl(mvd_handle* h, int n, int variant, int mean) {
     if (B.w) bad("combined updates take no weights (weights apply to sequential view-updates)");
   if (n == 0) return;
   ensure_combined(h);
-  prepare_run(h, variant, n, false, true);
+  prepare_run(h, variant, n);
   const bool geo = mean == MVD_MEAN_GEOMETRIC;
-  if (replay(h)) {
+  if (h->lanes.size() > 1) {
+    run_lanes(h, lane_key(h, geo ? 1 : 2, variant, 1), n, [&](int l, hipStream_t s) {
+      for (int b = 0; b < (int)h->blocks.size(); ++b)
+        if (h->block_lane[b] == l) enqueue_combined_block(h, s, variant, geo, b);
+    });
+  } else if (replay(h)) {
     hipGraphExec_t ex = graph_for(h, variant, geo ? 1 : 2);
     for (int i = 0; i < n; ++i) HIPCHECK(hipGraphLaunch(ex, h->stream));
   } else {
@@ -3125,7 +3195,10 @@ int mvd_view_update(mvd_handle* h, int view, int variant) {
     if (view < 0 || view >= h->nviews) bad("view index out of range");
     h->rec_token = 0;
     prepare_run(h, variant, 0);
-    enqueue_view(h, h->stream, variant, view);
+    if (h->spec_tp && !h->tp_even)
+      over_blocks(h, h->stream, [&](int b, hipStream_t s) { enqueue_view_block(h, s, variant, view, b); });
+    else
+      enqueue_view(h, h->stream, variant, view);
     finish_run(h);
   });
 }

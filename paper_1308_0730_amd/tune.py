@@ -9,7 +9,9 @@ against the per-length plans for all three kinds under each schedule (pass
 major, block major, run major: with the per-length plans each block lane
 runs its blocks without joining the other lanes after every pass, and the
 block-major schedules keep a few blocks in the memory-side cache from pass
-to pass, gains the per-pass profile cannot see), and keeps the fastest.
+to pass, gains the per-pass profile cannot see), and keeps the fastest.  A
+handle that runs the two-pass form with its shapes at create times whole runs
+with those too (the profile times the four passes only).
 The estimates are restored afterwards.  Results are cached in a JSON file keyed by GPU
 architecture, volume dims, view count and variant.
 """
@@ -88,14 +90,15 @@ def autotune(d, variant="eff", iters=1, cache_path=DEFAULT_CACHE, use_cache=True
             best = list(tiles)
             timings["run"] = {f"{list(t)}/{sch}": ms for (t, sch), ms in res.items()}
     tiles = best
-    if len(set(d.dims)) == 1:  # handles that may run the two-pass form
-        trials = [(best, schedule), (None, "pass")]
+    d.default_tiles().iterate(1, variant)
+    if any(d.two_pass_split(b) for b in range(len(d.dims))):
+        # the shapes at create, with which the handle runs the two-pass form
+        trials = [(best, schedule)] + [(None, sch) for sch in (("pass", "block", "run") if len(d.dims) > 1 else ("pass",))]
         res = [_run_ms(d, t, sch, variant, runs) for t, sch in trials]
-        timings["defaults"] = {"tuned": res[0], "defaults": res[1]}
+        timings["defaults"] = {"tuned": res[0], **{sch: ms for (_, sch), ms in zip(trials[1:], res[1:])}}
         if verbose:
-            print(f"[tune] whole run of {runs}: tuned {res[0]:.4f} ms, defaults {res[1]:.4f} ms", file=sys.stderr,
-                  flush=True)
-        tiles, schedule = trials[res[1] < res[0]]
+            print(f"[tune] whole run of {runs}: {timings['defaults']}", file=sys.stderr, flush=True)
+        tiles, schedule = trials[res.index(min(res))]
     _set(d, tiles)
     best = list(d.tiles())
     d.set_schedule(schedule)

@@ -150,3 +150,54 @@ def test_captured_runs_keep_their_memory(mvd):
         np.testing.assert_array_equal(out, e.iterate(3, "rl").estimate().cpu().numpy())
         L.mvd_destroy(h)
     assert a.live == 0
+
+
+# (540, 12, 10) and (16, 3, 8) have no two-pass form: half-rows past its row
+# plans, and too few rows for its smallest split; two blocks are equal
+UNEVEN = [(48, 45, 16), (540, 12, 10), (30, 27, 25), (16, 3, 8), (64, 32, 20), (30, 27, 25)]
+
+
+@pytest.mark.parametrize("variant,weights", [("rl", True), ("eff", False)])
+@pytest.mark.parametrize("graphs", [False, True])
+def test_uneven_blocks_take_their_own_form(mvd, graphs, variant, weights):
+    """Every block of a batch of different extents runs in the form that it
+    has alone, with its bits, under every schedule, in combined updates and in
+    view-updates, with the four-pass blocks beside it."""
+    from oracle import mvd_oracle as O
+    blocks = [problem(dims, 2, 850 + i, weights) for i, dims in enumerate(UNEVEN)]
+    # a run, single iterations and view-updates, a combined update
+    steps = [lambda d: d.iterate(3, variant), lambda d: d.iterate(1, variant),
+             lambda d: d.view_update(0, variant).view_update(1, variant)]
+    if not weights:
+        steps += [lambda d: d.iterate_combined(2, variant, "geometric"),
+                  lambda d: d.iterate_combined(1, variant, "arithmetic")]
+    refs, scales, flux = [], [], np.zeros((len(steps), 2))
+    for v, p, w in blocks:
+        with mvd.Deconvolver(v, p, w) as d:
+            scales.append(d.stats()["scale"])
+            out = []
+            for i, f in enumerate(steps):
+                out.append(f(d).estimate().cpu().numpy())
+                flux[i] += d.stats()["flux"]
+            refs.append((d.two_pass_split(), out))
+    assert [r[0] > 0 for r in refs] == [True, False, True, False, True, True]
+    with mvd.Deconvolver.batch(blocks, use_graphs=graphs) as b:
+        for sch in ("pass", "block", "run"):
+            b.set_schedule(sch)
+            for i, (v, _, _) in enumerate(blocks):
+                b.set_estimate(np.full_like(v[0], scales[i]), i)
+            for j, f in enumerate(steps):
+                f(b)
+                np.testing.assert_allclose(b.stats()["flux"], flux[j], rtol=1e-6)
+                for i, (split, out) in enumerate(refs):
+                    assert b.two_pass_split(i) == split
+                    got = b.estimate(i).cpu().numpy()
+                    if split:
+                        np.testing.assert_array_equal(got, out[j])
+                    else:
+                        assert O.rel_l2(got, out[j]) <= 1e-5
+        # set shapes: four passes everywhere, the profiler in between
+        b.set_tiles(*b.tiles()).iterate(1, variant)
+        assert not any(b.two_pass_split(i) for i in range(len(blocks)))
+        b.default_tiles().iterate(1, variant)
+        assert [b.two_pass_split(i) for i in range(len(blocks))] == [r[0] for r in refs]
