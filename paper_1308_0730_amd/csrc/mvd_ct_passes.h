@@ -331,7 +331,7 @@ __global__ void __launch_bounds__(T)
   __shared__ float2 lds[L * TX];
   __shared__ float2 s_tw[L];
   int local;
-  const int jid = find_job(jobs, njobs, PASS_Z, TX, local, false, true);
+  const int jid = find_job(jobs, njobs, PASS_Z, TX, local, false, jobs[0].z_back);
   if (jid < 0) return;
   const JobDesc& J = jobs[jid];
   if (v >= J.nviews) return;
@@ -389,7 +389,7 @@ __global__ void __launch_bounds__(T)
   __shared__ float2 lds[LMAX * TX];
   __shared__ float2 s_tw[LMAX];
   int local;
-  const int jid = find_job(jobs, njobs, PASS_Z, TX, local, false, true);
+  const int jid = find_job(jobs, njobs, PASS_Z, TX, local, false, jobs[0].z_back);
   if (jid < 0) return;
   const JobDesc& J = jobs[jid];
   if (v >= J.nviews) return;

@@ -16,7 +16,7 @@ namespace mvdk {
 // of an embryo-sized spectrum).  With last_job_first the jobs are taken from
 // the last, each in ascending tiles: the z passes of several jobs start on
 // the job that the forward y pass wrote last and end on the one that the
-// inverse y pass reads first.
+// inverse y pass reads first (the host decides, z_last_job_first).
 __device__ __forceinline__ int find_job(const JobDesc* __restrict__ jobs, int njobs, int kind,
                                         int param, int& local, bool reverse = false, bool last_job_first = false) {
   int t = reverse ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;

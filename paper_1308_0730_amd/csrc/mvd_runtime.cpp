@@ -748,8 +748,27 @@ void tp_upload(mvd_handle* h);
 // Transform length of a pass kind in a block: x the half-row nx/2, y ny, z nz.
 int job_len(const Block& B, int kind) { return kind == PASS_X ? B.M : kind == PASS_Y ? B.ny : B.nz; }
 
+// Whether z passes over several jobs start on the last one (see find_job).
+// It pays where the spectra of a launch do not all stay in the 256 MB
+// memory-side cache: ms per iteration of two views, first / last job first, 8
+// blocks of 512x256x128 (539 MB) 3.92 / 3.66, 3 of 512x512x128 (404 MB) 2.95 /
+// 2.81, 2 of 864x320x240 4.14 / 3.96, 6 of 864x400x405 (3.4 GB) 29.5 / 29.3.
+// Below it costs up to 1 %: 4 of 512x256x128 (269 MB) 1.77 / 1.79, 2 of
+// 256x256x160 0.671 / 0.680.  The lanes of uneven blocks run apart and
+// showed no difference.
+bool z_last_job_first(const mvd_handle* h) {
+  size_t bytes = 0;
+  for (const auto& B : h->blocks) {
+    const Block& A = h->blocks[0];
+    if (!h->blocked && (B.nx != A.nx || B.ny != A.ny || B.nz != A.nz)) return false;
+    bytes += (size_t)B.spec_elems * 2 * sizeof(float);
+  }
+  return bytes > (size_t)300 << 20;
+}
+
 void build_jobs(mvd_handle* h) {
   h->jobs.clear();
+  const int z_back = z_last_job_first(h);
   for (auto& B : h->blocks) {
     JobDesc j{};
     j.nx = B.nx;
@@ -778,6 +797,7 @@ void build_jobs(mvd_handle* h) {
     j.saved = B.saved;
     j.eps = B.eps;
     j.lamp = B.lamp;
+    j.z_back = z_back;
     if (h->blocked) {
       // the block's grid is a window of the volume's estimate
       const auto& T = h->tl;

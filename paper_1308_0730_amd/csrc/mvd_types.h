@@ -70,6 +70,7 @@ struct JobDesc {
   int ox, oy, oz;
   int hx, hy, hz;
   int ex, ey, ez;
+  int z_back;  // multi-job z passes take the last job first (see find_job)
 };
 
 // Two-pass form of a convolution (mvd_two_pass.h).  The y transform of a

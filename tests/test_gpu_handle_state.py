@@ -201,3 +201,22 @@ def test_uneven_blocks_take_their_own_form(mvd, graphs, variant, weights):
         assert not any(b.two_pass_split(i) for i in range(len(blocks)))
         b.default_tiles().iterate(1, variant)
         assert [b.two_pass_split(i) for i in range(len(blocks))] == [r[0] for r in refs]
+
+
+@pytest.mark.parametrize("dims,nb", [((512, 512, 128), 3), ((512, 256, 128), 4)])
+def test_job_order_of_the_z_passes(mvd, dims, nb):
+    """Equal four-pass blocks whose spectra together exceed the memory-side
+    cache (the z passes start on the last block) and do not (they start on
+    the first) give the plain handles' bits."""
+    import torch
+    nx, ny, nz = dims
+    g = torch.Generator(device="cuda")
+    g.manual_seed(870)
+    blocks = [([torch.rand((nz, ny, nx), device="cuda", generator=g) + 0.5],
+               [torch.rand((5, 7, 9), device="cuda", generator=g) + 0.1], None) for _ in range(nb)]
+    with mvd.Deconvolver.batch(blocks) as b:
+        b.iterate(2, "rl")
+        for i, (v, p, _) in enumerate(blocks):
+            with mvd.Deconvolver(v, p) as d:
+                assert b.two_pass_split(i) == d.two_pass_split() == 0
+                assert torch.equal(b.estimate(i), d.iterate(2, "rl").estimate())
