@@ -26,6 +26,10 @@ import torch
 from . import mvd
 
 KIND_PASSES = {0: ("x_ratio", "x_update"), 1: ("y_forward", "y_inverse"), 2: ("z_product",)}
+# Of the cached entries: what was tried for them.  Entries of another version
+# (or of none) are tuned again, since they may pin shapes that were never
+# timed against a form the library has gained.
+VERSION = 2
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "mvd_tiles.json")
 
 
@@ -48,8 +52,8 @@ def autotune(d, variant="eff", iters=1, cache_path=DEFAULT_CACHE, use_cache=True
     launch of the kind's passes; ms per run of `runs` iterations)."""
     key = _key(d, variant)
     cache = _load(cache_path) if cache_path else {}
-    if use_cache and key in cache:
-        _set(d, cache[key]["tiles"] if not cache[key].get("default") else None)
+    if use_cache and cache.get(key, {}).get("version") == VERSION:
+        _set(d, None if cache[key]["default"] else cache[key]["tiles"])
         d.set_schedule(cache[key].get("schedule", "pass"))
         return tuple(d.tiles()), cache[key].get("timings", {})
     d.set_schedule("pass")
@@ -105,7 +109,7 @@ def autotune(d, variant="eff", iters=1, cache_path=DEFAULT_CACHE, use_cache=True
     for b, e in enumerate(saved):
         d.set_estimate(e, b)
     if cache_path:
-        cache[key] = {"tiles": best, "default": tiles is None, "schedule": schedule, "timings": timings}
+        cache[key] = {"version": VERSION, "tiles": best, "default": tiles is None, "schedule": schedule, "timings": timings}
         os.makedirs(os.path.dirname(cache_path), exist_ok=True)
         with open(cache_path, "w") as f:
             json.dump(cache, f, indent=1)
