@@ -123,7 +123,6 @@ typedef void (*mvd_free_fn)(void* ptr, void* ctx);
  *              keeps to the four passes from then on, see mvd_set_tiles).
  *              Such a graph may be replayed between the handle's other calls;
  *              each captured run starts from the estimate at its replay.
- *              Launch shapes set later need a new capture.
  *   tile_config  0 = autotuned/default pass shapes; k > 0 forces candidate k-1
  *   boundary   MVD_BOUNDARY_CIRCULAR (0): the volume is one period of a
  *              periodic grid (the convolutions wrap around);
@@ -343,8 +342,9 @@ int mvd_set_psfs(mvd_handle* h, const float* const* psfs, const int* psf_dims, i
  * of one call of n.  The one exception is memory: once an allocation for the
  * spectra fails, or another one fails and they are given back for it, the
  * handle takes the four passes, whose results differ from the two-pass form's
- * in their rounding.  mvd_two_pass_split tells which form a block's last run
- * took: the split of ny of the two-pass form (>= 1), or 0. */
+ * in their rounding, until mvd_default_tiles.  mvd_two_pass_split tells which
+ * form a block's last run took: the split of ny of the two-pass form (>= 1),
+ * or 0. */
 int mvd_tile_candidates(int kind, int max_len, int* out, int cap);
 int mvd_tile_shape(int kind, int cfg, int* threads, int* per_tile, int* max_len, int* exact_len);
 int mvd_set_tiles(mvd_handle* h, int cfg_x, int cfg_y, int cfg_z);

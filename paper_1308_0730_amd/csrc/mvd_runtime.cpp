@@ -155,6 +155,8 @@ struct mvd_handle {
     int off = 0;      // x tiles of the blocks before it
   };
   bool tp_planned = false;                // some block has the form
+  bool tp_denied = false;                 // no memory for it, or none to be had under a capture:
+                                          // four passes, until mvd_default_tiles
   bool tiles_chosen = false;  // launch shapes were set (mvd_set_tiles): four-pass
   TpJob* d_tp = nullptr;                  // allocated, with the rest, on first use (ensure_two_pass)
   Partial* d_tp_parts = nullptr;
@@ -263,7 +265,7 @@ struct mvd_handle {
     bytes = (bytes + 255) & ~size_t(255);
     void* p = raw_alloc(bytes);
     if (!p && !tp_allocating && tp_release()) {
-      tp_planned = false;  // the four passes from here on
+      tp_denied = true;
       p = raw_alloc(bytes);
     }
     if (!p)
@@ -1736,7 +1738,7 @@ bool ensure_two_pass(mvd_handle* h, int role) {
   h->tp_allocating = false;
   if (!ok) {
     (void)h->tp_release();
-    h->tp_planned = false;
+    h->tp_denied = true;
     return false;
   }
   tp_upload(h);
@@ -1753,11 +1755,11 @@ bool ensure_two_pass(mvd_handle* h, int role) {
 // handle's plan alone decides, so that a call gives the same bits whatever
 // ran before it.
 bool use_two_pass(mvd_handle* h, int role, int n, bool capturing) {
-  if (!h->tp_planned || h->tiles_chosen) return false;
+  if (!h->tp_planned || h->tp_denied || h->tiles_chosen) return false;
   if (capturing && !(h->k2_built[ROLE_P] && h->k2_built[role])) {
-    // nothing can be allocated or built now: four passes, from here on, so
-    // that later runs leave the form that the captured ones expect
-    h->tp_planned = false;
+    // nothing can be allocated or built now; later runs give the bits of the
+    // captured ones
+    h->tp_denied = true;
     return false;
   }
   h->tp_asked += std::max(n, 1);
@@ -3331,6 +3333,7 @@ int mvd_default_tiles(mvd_handle* h) {
   return guard(h, [&] {
     set_tiles(h, pick_cfg(h, PASS_X), pick_cfg(h, PASS_Y), pick_cfg(h, PASS_Z));
     h->tiles_chosen = false;
+    h->tp_denied = false;
   });
 }
 

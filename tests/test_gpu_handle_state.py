@@ -220,3 +220,34 @@ def test_job_order_of_the_z_passes(mvd, dims, nb):
             with mvd.Deconvolver(v, p) as d:
                 assert b.two_pass_split(i) == d.two_pass_split() == 0
                 assert torch.equal(b.estimate(i), d.iterate(2, "rl").estimate())
+
+
+def test_default_tiles_bring_back_a_form_given_up(mvd):
+    """A handle that gave up the two-pass form for want of memory takes it
+    again after mvd_default_tiles, with its bits."""
+    import ctypes as C
+    from tests.test_gpu_failures import CappedAllocator, create
+    v, p, _ = problem((48, 45, 16), 2, 880, False)
+    L, a, out = mvd.lib(), CappedAllocator(mvd, 1 << 40), np.empty_like(v[0])
+    with mvd.Deconvolver(v, p) as e:
+        want, start = e.iterate(2, "rl").estimate().cpu().numpy(), np.full_like(v[0], e.stats()["scale"])
+    rc, h = create(mvd, v, p, a)
+    assert rc == mvd.MVD_OK
+
+    def run():
+        assert L.mvd_set_estimate(h, start.ctypes.data_as(C.c_void_p), mvd.MEM_HOST, 0) == mvd.MVD_OK
+        assert L.mvd_iterate(h, 2, 0) == mvd.MVD_OK
+        assert L.mvd_get_estimate(h, out.ctypes.data, mvd.MEM_HOST, 0) == mvd.MVD_OK
+        return L.mvd_two_pass_split(h, 0) > 0
+
+    assert run()
+    a.cap = a.live
+    assert L.mvd_iterate(h, 1, 2) == mvd.MVD_OK  # its kernel planes take the place of the spectra
+    assert not run()
+    a.cap = 1 << 40
+    assert not run()
+    assert L.mvd_default_tiles(h) == mvd.MVD_OK
+    assert run()
+    np.testing.assert_array_equal(out, want)
+    L.mvd_destroy(h)
+    assert a.live == 0
