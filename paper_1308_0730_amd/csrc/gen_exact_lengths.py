@@ -97,13 +97,14 @@ def row_radices(M):
 
 
 def row_forward_radices(M):
-    """Radices of the modes without an update epilogue (forward, ratio) at
+    """Radices of the ratio mode and of the block-wise form's forward mode at
     the same rows per wave: composite ones between 256 and 512 points where
     the cost model of the two-pass rows saves 8 % or more (432 points: 9 x 6 x 8
     instead of 4 x 4 x 3 x 3 x 3).  Rows this long fill a large radix's stage
     without further rows per wave.  The update passes, which hold two
     operands, keep the small radices: the larger ones take them past 128
-    registers."""
+    registers; so do the volumes' forward passes, which have to leave the
+    update's bits."""
     small, rpw = row_radices(M), row_rows(M)
     if not 256 < M <= 512:
         return small
@@ -224,7 +225,7 @@ def main():
         end = " \\" if i + 1 < len(tps) else ""
         rpw, rad = tp_row_plan(M)
         lines.append(f"  X({M}, {rpw}, {', '.join(map(str, rad))}){end}")
-    lines += ["", "// X(M, waves per workgroup, rows per wave, radices...) of the forward and ratio modes",
+    lines += ["", "// X(M, waves per workgroup, rows per wave, radices...) of the ratio and the windows' forward modes",
               "#define MVD_EXACT_ROW_FWD(X) \\"]
     for i, M in enumerate(rows):
         end = " \\" if i + 1 < len(rows) else ""

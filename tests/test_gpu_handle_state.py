@@ -251,3 +251,16 @@ def test_default_tiles_bring_back_a_form_given_up(mvd):
     np.testing.assert_array_equal(out, want)
     L.mvd_destroy(h)
     assert a.live == 0
+
+
+@pytest.mark.parametrize("dims", [(48, 45, 16), (512, 16, 12), (512, 3, 8), (540, 12, 10), (720, 10, 8), (864, 12, 10),
+                                  (1000, 8, 6), (1024, 8, 6)])
+def test_a_saved_estimate_continues_with_the_same_bits(mvd, dims):
+    """A run continued from a saved estimate (whose spectrum a forward pass
+    computes) gives the bits of the unbroken one (whose update pass left it)."""
+    v, p, w = problem(dims, 2, 890, True)
+    with mvd.Deconvolver(v, p, w) as d:
+        saved = d.iterate(2, "eff").estimate().cpu().numpy()
+        went_on = d.iterate(2, "eff").estimate().cpu().numpy()
+        d.set_estimate(saved)
+        np.testing.assert_array_equal(d.iterate(2, "eff").estimate().cpu().numpy(), went_on)
