@@ -166,3 +166,37 @@ def test_new_psfs_reach_the_two_pass_spectra(mvd):
         np.testing.assert_array_equal(d.iterate(2, "eff").estimate().cpu().numpy(),
                                       e.set_estimate(np.full_like(v[0], d.stats()["scale"]))
                                       .iterate(2, "eff").estimate().cpu().numpy())
+
+
+# (nx, ny, nz), split: volumes past 1.5 Mi spectrum values (every split; the
+# largest planes and volumes of the form), then the splits of small ones that
+# SHAPES leaves out and both sides of the small rule's line
+SPLITS = [((512, 25, 256), 1), ((512, 50, 256), 2), ((400, 162, 50), 3), ((256, 96, 128), 4), ((320, 250, 128), 5),
+          ((180, 144, 125), 6), ((216, 240, 200), 8), ((180, 288, 200), 9), ((24, 54, 10), 6), ((24, 48, 8), 6),
+          ((400, 243, 32), 3), ((400, 324, 25), 3), ((540, 4, 4), 0), ((512, 250, 64), 2), ((512, 256, 81), 0),
+          ((64, 300, 300), 0)]
+
+
+@pytest.mark.parametrize("i", range(len(SPLITS)))
+def test_two_pass_splits(mvd, i):
+    """The form runs where its rule says, with every variant with and without
+    weights, and gives the oracle's iteration."""
+    dims, split = SPLITS[i]
+    variant, weights, lam = (O.RL, O.EFF, O.OPT1, O.OPT2)[i % 4], bool(i // 4 & 1), 0.0006 * (i % 3 == 0)
+    v, p, w = problem(dims, 2, 1000 + i, weights)
+    with mvd.Deconvolver(v, p, w, lam=lam) as d:
+        got = d.iterate(1, variant).estimate().cpu().numpy()
+        assert d.two_pass_split() == split
+    assert O.rel_l2(got, O.run(v, p, 1, variant, lam=lam, weights=w)) <= 1e-5
+
+
+@pytest.mark.parametrize("dims,variant", [((216, 200, 100), O.OPT1), ((60, 50, 40), O.RL)])
+def test_two_pass_of_a_padded_grid(mvd, dims, variant):
+    """The linear boundary: the form runs on the padded grid, whose margin
+    voxels carry no data."""
+    v, p, w = problem(dims, 2, 1030, True)
+    ref = O.ProblemLinear(v, p, w, 0.0006)
+    with mvd.Deconvolver(v, p, w, lam=0.0006, boundary="linear") as d:
+        got = d.iterate(1, variant).estimate().cpu().numpy()
+        assert d.two_pass_split() > 0
+    assert O.rel_l2(got, ref.interior(ref.iterate(ref.psi0(), 1, variant))) <= 1e-5
