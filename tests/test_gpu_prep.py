@@ -77,3 +77,44 @@ def test_compound_adjoint_on_the_device_is_the_hosts(mvd, variant, exts):
     assert r0 == 0 and r1 > 0
     for x, y in zip(dev, host):
         np.testing.assert_allclose(x, y, rtol=0, atol=1e-9 * np.abs(y).max())
+
+
+@pytest.mark.parametrize("dims,exts", [((32, 30, 27), [(7, 5, 9)] * 3), ((40, 36, 30), [(23, 21, 19), (17, 25, 9)]),
+                                       ((30, 24, 20), [(5, 4, 7), (5, 3, 2), (1, 1, 1)])])
+@pytest.mark.parametrize("variant", [O.RL, O.EFF, O.OPT1, O.OPT2])
+def test_device_planes_are_the_hosts(mvd, dims, exts, variant):
+    """One iteration with the kernels prepared on the device and by the host
+    code (its scratch refused).  The PSFs' own planes have the same bits.  The
+    compound kernels' FP64 sums differ in order, 1e-16 of their size, so hardly
+    an FP32 rounding of the planes differs and at most a tenth of the voxels,
+    by one FP32 step (6e-8): 2e-8 in relative L2, where planes prepared in FP32
+    would differ by some 1e-7."""
+    from tests.test_gpu_failures import CappedAllocator, create
+    v, p = problem(dims, exts, 740)
+    q = [x[::-1].copy() for x in p]
+    L, P = mvd.lib(), C.POINTER(C.c_void_p)
+
+    def run(refuse):
+        a, cfg, out = CappedAllocator(mvd, 1 << 40), (C.c_int * 3)(), np.empty_like(v[0])
+        rc, h = create(mvd, v, p, a)
+        assert rc == mvd.MVD_OK
+        assert L.mvd_get_tiles(h, cfg) == L.mvd_set_tiles(h, *cfg) == mvd.MVD_OK  # four passes: no other memory
+        assert L.mvd_iterate(h, 1, variant) == mvd.MVD_OK
+        start = np.ones_like(v[0])
+        assert L.mvd_set_estimate(h, start.ctypes.data_as(C.c_void_p), mvd.MEM_HOST, 0) == mvd.MVD_OK
+        if refuse:
+            a.cap = a.live
+        ptrs = (C.c_void_p * len(q))(*[x.ctypes.data for x in q])
+        dd = (C.c_int * (3 * len(q)))(*sum([list(x.shape[::-1]) for x in q], []))
+        assert L.mvd_set_psfs(h, C.cast(ptrs, P), dd, mvd.MEM_HOST) == mvd.MVD_OK
+        assert L.mvd_iterate(h, 1, variant) == mvd.MVD_OK
+        assert L.mvd_get_estimate(h, out.ctypes.data, mvd.MEM_HOST, 0) == mvd.MVD_OK
+        L.mvd_destroy(h)
+        return out, a.refused
+
+    (dev, r0), (host, r1) = run(False), run(True)
+    assert r0 == 0 and r1 == (1 if variant == O.RL else 2)
+    if variant == O.RL:
+        np.testing.assert_array_equal(dev, host)
+    else:
+        assert O.rel_l2(dev, host) <= 2e-8
