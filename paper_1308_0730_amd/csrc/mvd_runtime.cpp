@@ -2739,16 +2739,21 @@ void set_psfs_impl(mvd_handle* h, const float* const* psfs, const int* psf_dims,
     dims.push_back({k[0], k[1], k[2]});
   }
   HIPCHECK(hipStreamSynchronize(h->stream));
+  Block W = B;  // with the new window; the handle keeps the old PSFs if there is no memory for it
+  W.P = P;
+  set_kernel_window(W);
+  float* H = nullptr;
+  if (W.kz > B.kz_cap) H = (float*)h->dalloc((size_t)N * W.h_elems * 2 * sizeof(float));
   B.P = std::move(P);
   B.psf_sum = std::move(sums);
   B.psf_dims = std::move(dims);
   set_kernel_window(B);
-  if (B.kz > B.kz_cap) {
+  if (H) {
     // a wider window: fresh kernel-plane arrays (the old ones are released
     // with the handle); the compound kernels are rebuilt on next use
     B.kz_cap = B.kz;
     for (int r = 0; r < N_ROLES; ++r) B.H[r] = nullptr;
-    B.H[ROLE_P] = (float*)h->dalloc((size_t)N * B.h_elems * 2 * sizeof(float));
+    B.H[ROLE_P] = H;
   }
   build_planes(h, B, MVD_RL, B.H[ROLE_P]);
   for (int r = 1; r < N_ROLES; ++r) h->built[r] = false;

@@ -264,3 +264,33 @@ def test_a_saved_estimate_continues_with_the_same_bits(mvd, dims):
         went_on = d.iterate(2, "eff").estimate().cpu().numpy()
         d.set_estimate(saved)
         np.testing.assert_array_equal(d.iterate(2, "eff").estimate().cpu().numpy(), went_on)
+
+
+def test_psfs_that_find_no_memory_leave_the_old_ones(mvd):
+    """PSFs with a longer z window than the handle has room for: ENOMEM, and
+    the handle runs on with the PSFs it has."""
+    import ctypes as C
+    from tests.test_gpu_failures import CappedAllocator, create
+    v, p, _ = problem((48, 45, 16), 2, 900, False)
+    big = [np.ones((15, 7, 9), np.float32) for _ in p]
+    L, a, out = mvd.lib(), CappedAllocator(mvd, 1 << 40), np.empty_like(v[0])
+    rc, h = create(mvd, v, p, a)
+    assert rc == mvd.MVD_OK
+    assert L.mvd_iterate(h, 2, 1) == mvd.MVD_OK
+    cfg = (C.c_int * 3)()
+    assert L.mvd_get_tiles(h, cfg) == mvd.MVD_OK
+    for tiles in (False, True):
+        if tiles:
+            assert L.mvd_set_tiles(h, *cfg) == mvd.MVD_OK
+        a.cap = 0
+        ptrs = (C.c_void_p * 2)(*[x.ctypes.data for x in big])
+        dims = (C.c_int * 6)(*([9, 7, 15] * 2))
+        assert L.mvd_set_psfs(h, C.cast(ptrs, C.POINTER(C.c_void_p)), dims, mvd.MEM_HOST) == mvd.MVD_ENOMEM
+        a.cap = 1 << 40
+        assert L.mvd_iterate(h, 2, 1) == mvd.MVD_OK
+    assert L.mvd_get_estimate(h, out.ctypes.data, mvd.MEM_HOST, 0) == mvd.MVD_OK
+    L.mvd_destroy(h)
+    with mvd.Deconvolver(v, p) as d:
+        # the failed call gave the two-pass form's memory back: four passes since
+        d.iterate(2, "eff").set_tiles(*cfg).iterate(4, "eff")
+        np.testing.assert_array_equal(out, d.estimate().cpu().numpy())
