@@ -545,8 +545,11 @@ struct PrepFactors {
   }
 };
 
-// Correlations above this many FMAs (about a quarter of a second) stay with
-// the host's separable transforms, whose work grows more slowly.
+// Correlations above this many FMAs (about 70 ms) stay with the host's
+// separable transforms, whose work grows more slowly.  Device / host, ms of a
+// whole preparation: six views of 31^3 (2.7e10 FMAs, Optimization I) 6.2 / 60,
+// of 47^3 (3.2e11) 53 / 260; two of 73^3 (3.0e11) 57 / 929; four of 41^3 (EFF,
+// 2.0e11) 36 / 272.
 constexpr double kPrepMaxFmas = 4e11;
 
 // Kernel planes of every view on the device (variant MVD_RL: the PSFs'
