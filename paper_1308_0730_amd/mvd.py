@@ -233,16 +233,20 @@ class Deconvolver:
         if device is None:
             device = torch.device("cuda", torch.cuda.current_device())
         self.device = torch.device(device)
-        self._bufs = {}
+        self._h, self._bufs = None, {}
         dev = self.device
 
         def _alloc(nbytes, ctx):
             # from the pool of the handle's stream, whichever stream is
             # current at a lazy allocation: the caching allocator reuses a
-            # block in the order of the stream it was allocated on only
+            # block in the order of the stream it was allocated on only (at
+            # create the handle's stream is the current one)
             try:
-                with torch.cuda.stream(self.stream):
+                if self._h is None or torch.cuda.current_stream(dev) == self.stream:
                     t = torch.empty(int(nbytes), dtype=torch.uint8, device=dev)
+                else:
+                    with torch.cuda.stream(self.stream):
+                        t = torch.empty(int(nbytes), dtype=torch.uint8, device=dev)
             except RuntimeError:
                 return None
             self._bufs[t.data_ptr()] = t
