@@ -35,7 +35,8 @@ KERNEL_SOURCES = tuple("paper_1308_0730_amd/csrc/" + f for f in (
     "mvd_exact_x_win.hip",
     "mvd_exact_class.hip",
     "mvd_exact_y.hip", "mvd_exact_z.hip", "mvd_exact_lengths.h", "fft_engine.h", "fft_ct.h", "mvd_device.h",
-    "mvd_gmem.h", "mvd_types.h", "fft_small_tw.h"))
+    "mvd_gmem.h", "mvd_types.h", "fft_small_tw.h", "mvd_two_pass.h", "mvd_tp_plane.hip", "mvd_tp_x.hip",
+    "mvd_tp_x_update.hip", "mvd_tp_x_comb.hip", "mvd_prep.hip"))
 
 
 def workload(cfg):
@@ -174,7 +175,7 @@ def pass_of_kernel(name):
 
 
 def _short(name, n=150):
-    name = re.sub(r"\(.*\)$", "", name)
+    name = re.sub(r"\(.*\)$", "", name.replace("(anonymous namespace)::", ""))
     name = re.sub(r"((?:mvdk::)?ColPlan<[^>]*>, )+(?:mvdk::)?ColPlan<[^>]*>", "ColPlan<L>...", name)
     return name if len(name) <= n else name[:n] + "..."
 
@@ -222,7 +223,8 @@ def summarize_sq_counters(d, title, command, top=20):
         n[k][c] = n[k].get(c, 0) + 1
     counters = sorted({c for k in agg for c in agg[k]})
     key = "SQ_INSTS_VALU" if "SQ_INSTS_VALU" in counters else counters[0]
-    names = [k for k in names if pass_of_kernel(k)]
+    # the passes, the two-pass form's and the preparation's kernels
+    names = [k for k in names if pass_of_kernel(k) or re.search(r"k_(xpass_tp|plane|corr|compound|kernel_planes)", k)]
     names.sort(key=lambda k: -agg[k].get(key, 0.0))
     lines = [f"# rocprofv3 SQ counters per launch: {title}", f"# command: {command}",
              f"# source_hash: {source_hash()}", "# name | launches | " + " | ".join(counters)]
