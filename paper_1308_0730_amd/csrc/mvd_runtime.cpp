@@ -124,9 +124,9 @@ struct mvd_handle {
   };
   // side streams (default priority).  Every block has a lane (longest
   // processing time first over the blocks' voxel counts), so all groups of a
-  // block run on one stream in pass order: a sequential iteration forks the
-  // side streams once and joins them at its end (defer_join); other
-  // sequences fork and join around every pass.
+  // block run on one stream in pass order: a run forks the side streams once
+  // and joins them at its end (run_lanes, defer_join); only the profiler and
+  // launch shapes without per-length plans fork and join around every pass.
   static constexpr int kSide = 15;
   int nside = 0;  // side lanes created: one per further block, at most kSide
   hipStream_t side[kSide] = {};
