@@ -335,8 +335,9 @@ int mvd_set_psfs(mvd_handle* h, const float* const* psfs, const int* psf_dims, i
  * selects them, mvd_profile times them, and mvd_default_tiles takes a handle
  * back to its shapes and form at create.
  *
- * The form depends on the volume's extents (batches of different extents with
- * the linear boundary take the four passes) and these calls, not on what ran
+ * The form depends on the blocks' extents and these calls (batches of different
+ * extents take the four passes with the linear boundary, and where several
+ * small blocks of a lane have no two-pass form), not on what ran
  * before: a call from the same estimate gives the same bits each time, and
  * n calls of one iteration, or of their view-updates in order, give the bits
  * of one call of n.  The one exception is memory: once an allocation for the
@@ -366,8 +367,7 @@ int mvd_two_pass_split(const mvd_handle* h, int block);
  *                            then the next; one graph per run
  * The block-major schedules take effect with the per-length plans for all
  * three pass kinds or in the two-pass form, and two or more blocks (otherwise
- * runs are pass-major); two-pass blocks of different extents take one launch
- * each under every schedule.  mvd_profile always runs pass-major.
+ * runs are pass-major).  mvd_profile always runs pass-major.
  * mvd_get_schedule returns the current one. */
 #define MVD_SCHEDULE_PASS_MAJOR 0
 #define MVD_SCHEDULE_BLOCK_MAJOR 1

@@ -144,15 +144,20 @@ struct mvd_handle {
   // updates of uneven blocks)
   std::vector<Group> bgroups[3];
   // two-pass convolutions (mvd_two_pass.h): planned at create, used until
-  // launch shapes are set; one launch covers every block of a pass where the
-  // blocks have equal extents, else one block, on its lane.  Uneven blocks
-  // choose each for itself: one without a two-pass form takes four passes in
-  // the same chain.
-  struct TpPass {
-    int grid = 0;     // tiles of the block (x: the four-pass ones where it has no two-pass form)
+  // launch shapes are set.  Uneven blocks choose each for itself: one
+  // without a two-pass form takes four passes in the same chain.
+  struct TpPass {  // one launch over n consecutive jobs of the table
+    int first = 0, n = 0;
+    int M = 0;        // x passes: the jobs' half-row
+    int grid = 0;
     int threads = 0;
     size_t lds = 0;
-    int off = 0;      // x tiles of the blocks before it
+    int off = 0;      // x passes: partial results of the jobs before
+  };
+  struct TpSet {   // the launches of a pass over a set of blocks
+    std::vector<int> blocks;
+    TpPass plane;
+    std::vector<TpPass> x;  // one per half-row and workgroup
   };
   bool tp_planned = false;                // some block has the form
   bool tp_denied = false;                 // no memory for it, or none to be had under a capture:
@@ -165,8 +170,9 @@ struct mvd_handle {
   int64_t tp_asked = 0;                   // iterations asked for in the two-pass form (use_two_pass)
   bool caller_graph = false;              // the caller has captured runs on the handle's stream (prepare_run)
   std::vector<TpJob> tpjobs;              // one per block
-  std::vector<TpPass> tp_x, tp_p;         // per block: the x and the plane pass
-  bool tp_even = false;                   // equal extents
+  std::vector<int> tp_order;              // the table: blocks by lane, half-row and x workgroup
+  std::vector<TpSet> tp_block, tp_lane;   // per block and per lane (its two-pass blocks)
+  std::vector<int> tp_off;                // partial results of a four-pass block's x passes
   int tp_tiles = 0;                       // x tiles of all blocks
   bool k2_built[N_ROLES] = {false, false, false, false};
   int stat_grid = 0;                      // the last run's partial results: x tiles
@@ -1210,33 +1216,76 @@ bool tp_plan_block(mvd_handle* h, const Block& B, const std::vector<FftPlan>& pl
   j.kg = mvd_cdiv(np, j.ks);
   j.mg_n1 = mvd_magic(j.n1), j.mg_nz = mvd_magic(B.nz);
   j.mg_a = mvd_magic(j.a), j.mg_kg = mvd_magic(j.kg), j.mg_R = mvd_magic(j.R);
-  x = {j.nz * j.atiles, 64 * w, lds_of(w), 0};
+  x.M = B.M, x.grid = j.nz * j.atiles, x.threads = 64 * w, x.lds = lds_of(w);
   // plane pass: whole SIMDs, two waves for planes too small to feed four
-  p = {j.yz_tiles, j.n1 * j.nz >= 1536 ? 256 : 128, tp_plane_lds(j.n1, j.nz), 0};
+  p.grid = j.yz_tiles, p.threads = j.n1 * j.nz >= 1536 ? 256 : 128, p.lds = tp_plane_lds(j.n1, j.nz);
   return true;
 }
 
+// The jobs of the two-pass form and its launches, per block and per lane.  A
+// plane pass takes jobs of any extents, an x pass those of one half-row and
+// workgroup: 96 blocks of 24 to 40 points per axis take 0.76 ms per iteration
+// of two views, with a launch per block 1.45 (in the four passes, which group
+// a lane's blocks too, 0.79).  Blocks without the form get a launch each; where
+// a lane has several small ones all blocks keep the four passes.
 void tp_plan(mvd_handle* h, const std::vector<FftPlan>& plans) {
+  using Pass = mvd_handle::TpPass;
   const int nb = (int)h->blocks.size();
   const Block& B = h->blocks[0];
-  bool any = false;
-  h->tp_even = true;
-  for (const auto& X : h->blocks) h->tp_even &= X.nx == B.nx && X.ny == B.ny && X.nz == B.nz;
-  if (h->linear && !h->tp_even) return;  // these give the bits of the per-length four-pass plans
+  bool even = true, any = false;
+  for (const auto& X : h->blocks) even &= X.nx == B.nx && X.ny == B.ny && X.nz == B.nz;
+  if (h->linear && !even) return;  // these give the bits of the per-length four-pass plans
   h->tpjobs.assign(nb, TpJob{});
-  h->tp_x.resize(nb), h->tp_p.resize(nb);
-  int64_t xt = 0, pt = 0;
+  h->tp_block.assign(nb, {});
+  h->tp_lane.assign(h->nside + 1, {});
+  h->tp_off.assign(nb, 0);
+  h->tp_order.resize(nb);
+  std::vector<Pass> x(nb), p(nb);
+  std::vector<int> small(h->nside + 1, 0);
   for (int b = 0; b < nb; ++b) {
-    if (tp_plan_block(h, h->blocks[b], plans, h->tp_even ? nb : 1, h->tpjobs[b], h->tp_x[b], h->tp_p[b])) {
+    h->tp_order[b] = b;
+    if (tp_plan_block(h, h->blocks[b], plans, even ? nb : 1, h->tpjobs[b], x[b], p[b])) {
       any = true;
     } else {
       h->blocks[b].tpR = 0;
       h->tpjobs[b] = TpJob{};
-      h->tp_x[b] = {h->bgroups[PASS_X][b].grid, 0, 0, 0};
+      if (h->blocks[b].V < (int64_t)1 << 20 && ++small[h->block_lane[b]] > 1) return;
     }
-    h->tp_x[b].off = (int)xt;
-    xt += h->tp_x[b].grid;
-    pt += (int64_t)h->tp_p[b].grid * h->nviews;
+  }
+  auto key = [&](int b) {
+    return std::array<int, 4>{h->block_lane[b], h->blocks[b].tpR == 0, x[b].M, x[b].threads};
+  };
+  std::stable_sort(h->tp_order.begin(), h->tp_order.end(), [&](int a, int b) { return key(a) < key(b); });
+  int64_t xt = 0, pt = 0;
+  auto join = [](Pass& to, const Pass& q) {
+    to.n += 1;
+    to.grid += q.grid;
+    to.threads = std::max(to.threads, q.threads);
+    to.lds = std::max(to.lds, q.lds);
+  };
+  for (int i = 0; i < nb; ++i) {
+    const int b = h->tp_order[i];
+    if (!h->blocks[b].tpR) {
+      h->tp_off[b] = (int)xt;
+      xt += h->bgroups[PASS_X][b].grid;
+    } else {
+      x[b].first = p[b].first = i;
+      x[b].n = p[b].n = 1;
+      x[b].off = (int)xt;
+      h->tp_block[b] = {{b}, p[b], {x[b]}};
+      auto& L = h->tp_lane[h->block_lane[b]];
+      if (L.blocks.empty())
+        L.plane = p[b];
+      else
+        join(L.plane, p[b]);
+      if (L.blocks.empty() || key(L.blocks.back()) != key(b))
+        L.x.push_back(x[b]);
+      else
+        join(L.x.back(), x[b]);
+      L.blocks.push_back(b);
+      xt += x[b].grid;
+    }
+    pt += (int64_t)p[b].grid * h->nviews;
     if (xt > 0x7fffffff || pt > 0x7fffffff) return;
   }
   h->tp_tiles = (int)xt;
@@ -1255,8 +1304,9 @@ void tp_upload(mvd_handle* h) {
     j.h_main = B.h_main, j.h_elems = B.h_elems;
     j.Mp = B.Mp, j.kz = B.kz, j.cz = B.cz;
   }
-  HIPCHECK(hipMemcpyAsync(h->d_tp, h->tpjobs.data(), h->tpjobs.size() * sizeof(TpJob), hipMemcpyHostToDevice,
-                          h->stream));
+  std::vector<TpJob> table;
+  for (int b : h->tp_order) table.push_back(h->tpjobs[b]);
+  HIPCHECK(hipMemcpyAsync(h->d_tp, table.data(), table.size() * sizeof(TpJob), hipMemcpyHostToDevice, h->stream));
   HIPCHECK(hipStreamSynchronize(h->stream));
 }
 
@@ -1747,8 +1797,9 @@ bool ensure_two_pass(mvd_handle* h, int role) {
   tp_upload(h);
   for (size_t b = 0; b < nb; ++b) {
     if (!h->blocks[b].tpR) continue;
-    const TpArgs a{h->d_tp + b, 1, h->d_tw, h->stream, h->tp_p[b].grid * h->nviews};
-    HIPCHECK(mvd_launch_plane_kernel(a, h->tp_p[b].lds, role, h->blocks[b].K2[role]));
+    const auto& p = h->tp_block[b].plane;
+    const TpArgs a{h->d_tp + p.first, 1, h->d_tw, h->stream, p.grid * h->nviews};
+    HIPCHECK(mvd_launch_plane_kernel(a, p.lds, role, h->blocks[b].K2[role]));
   }
   h->k2_built[role] = true;
   return true;
@@ -1778,26 +1829,25 @@ void finish_run(mvd_handle* h) {
   if (two_pass_once(h)) (void)h->tp_release();
 }
 
-// One launch of a pass of the two-pass form: blocks [b0, b0 + n), n > 1 only
-// where they have equal extents.
-void tp_launch_x(mvd_handle* h, hipStream_t s, int b0, int n, int mode, int v, int opt) {
-  const auto& x = h->tp_x[b0];
-  const TpArgs a{h->d_tp + b0, n, h->d_tw, s, n * x.grid};
-  Partial* parts = h->d_tp_parts + (size_t)v * h->tp_tiles + x.off;
-  HIPCHECK(mvd_launch_x_tp(a, h->tpjobs[b0].M, x.threads / 64, x.lds, mode, v, mode ? parts : nullptr, h->d_flags,
-                           opt));
+// The passes of the two-pass form over a set of blocks.
+void tp_x(mvd_handle* h, hipStream_t s, const mvd_handle::TpSet& set, int mode, int v, int opt) {
+  for (const auto& x : set.x) {
+    const TpArgs a{h->d_tp + x.first, x.n, h->d_tw, s, x.grid};
+    Partial* parts = h->d_tp_parts + (size_t)v * h->tp_tiles + x.off;
+    HIPCHECK(mvd_launch_x_tp(a, x.M, x.threads / 64, x.lds, mode, v, mode ? parts : nullptr, h->d_flags, opt));
+  }
 }
-void tp_launch_plane(mvd_handle* h, hipStream_t s, int b0, int n, int v, int role, int conj, int src_saved) {
-  const auto& p = h->tp_p[b0];
-  const TpArgs a{h->d_tp + b0, n, h->d_tw, s, n * p.grid};
+void tp_plane(mvd_handle* h, hipStream_t s, const mvd_handle::TpSet& set, int v, int role, int conj, int src_saved) {
+  const auto& p = set.plane;
+  if (!p.n) return;
+  const TpArgs a{h->d_tp + p.first, p.n, h->d_tw, s, p.grid};
   HIPCHECK(mvd_launch_plane(a, p.threads, p.lds, v, role, conj, src_saved));
 }
-// A view-update of blocks of equal extents.
-void tp_view(mvd_handle* h, hipStream_t s, int b0, int n, int v, int role, int conj_back) {
-  tp_launch_plane(h, s, b0, n, v, ROLE_P, 0, 0);
-  tp_launch_x(h, s, b0, n, 1, v, XOPT_SPEC);
-  tp_launch_plane(h, s, b0, n, v, role, conj_back, 0);
-  tp_launch_x(h, s, b0, n, 2, v, XOPT_SPEC);
+void tp_view(mvd_handle* h, hipStream_t s, const mvd_handle::TpSet& set, int v, int role, int conj_back) {
+  tp_plane(h, s, set, v, ROLE_P, 0, 0);
+  tp_x(h, s, set, 1, v, XOPT_SPEC);
+  tp_plane(h, s, set, v, role, conj_back, 0);
+  tp_x(h, s, set, 2, v, XOPT_SPEC);
 }
 
 // Per-launch event timing of the passes (profiling hook): kinds are
@@ -1827,8 +1877,8 @@ struct PassTimer {
 void enqueue_view_passes(mvd_handle* h, hipStream_t s, int variant, int v, PassTimer* t, bool spec_out) {
   const int role = variant == MVD_RL ? ROLE_P : variant;
   const int conj_back = variant == MVD_RL ? 1 : 0;
-  if (h->spec_tp && !t) {  // blocks of equal extents
-    tp_view(h, s, 0, (int)h->blocks.size(), v, role, conj_back);
+  if (h->spec_tp && !t) {  // blocks on one lane
+    tp_view(h, s, h->tp_lane[0], v, role, conj_back);
     return;
   }
   Partial* parts = h->d_parts + (size_t)v * h->grid_x;
@@ -1915,7 +1965,7 @@ void block_z(mvd_handle* h, hipStream_t s, int b, int v, int role, int conjH, in
 }
 // Partial results of a four-pass block's x passes.
 Partial* block_parts(mvd_handle* h, int b, int v) {
-  return h->spec_tp ? h->d_tp_parts + (size_t)v * h->tp_tiles + h->tp_x[b].off
+  return h->spec_tp ? h->d_tp_parts + (size_t)v * h->tp_tiles + h->tp_off[b]
                     : h->d_parts + (size_t)v * h->grid_x + h->bgroups[PASS_X][b].part_off;
 }
 
@@ -1926,7 +1976,7 @@ void enqueue_view_block(mvd_handle* h, hipStream_t s, int variant, int v, int b)
   const int role = variant == MVD_RL ? ROLE_P : variant;
   const int conj_back = variant == MVD_RL ? 1 : 0;
   if (two_pass(h, b)) {
-    tp_view(h, s, b, 1, v, role, conj_back);
+    tp_view(h, s, h->tp_block[b], v, role, conj_back);
     return;
   }
   Partial* parts = block_parts(h, b, v);
@@ -1956,7 +2006,21 @@ bool block_major(const mvd_handle* h) {
 // per lane, keep their spectra, views and estimates in the memory-side
 // cache from pass to pass.  Blocks are independent, so any such order gives
 // the same results; the lanes are forked once and joined at the end.
+//
+// The same for the pass-major schedule in the two-pass form: a pass of the
+// lane launches all its two-pass blocks, four-pass blocks follow one by one.
+void enqueue_lane_view(mvd_handle* h, hipStream_t s, int variant, int v, int lane) {
+  tp_view(h, s, h->tp_lane[lane], v, variant == MVD_RL ? ROLE_P : variant, variant == MVD_RL);
+  for (int b = 0; b < (int)h->blocks.size(); ++b)
+    if (h->block_lane[b] == lane && !h->blocks[b].tpR) enqueue_view_block(h, s, variant, v, b);
+}
+
 void enqueue_lane_blocks(mvd_handle* h, hipStream_t s, int variant, int n, int lane) {
+  if (h->schedule == MVD_SCHEDULE_PASS_MAJOR) {
+    for (int i = 0; i < n; ++i)
+      for (int v = 0; v < h->nviews; ++v) enqueue_lane_view(h, s, variant, v, lane);
+    return;
+  }
   std::vector<int> mine;
   for (int b = 0; b < (int)h->blocks.size(); ++b)
     if (h->block_lane[b] == lane) mine.push_back(b);
@@ -1985,43 +2049,31 @@ void over_lanes(mvd_handle* h, hipStream_t s, F&& f) {
       HIPCHECK(hipStreamWaitEvent(s, h->ev_join[l - 1], 0));
     }
 }
-// f(block, its lane's stream) for every block
-template <class F>
-void over_blocks(mvd_handle* h, hipStream_t s, F&& f) {
-  over_lanes(h, s, [&](int l, hipStream_t sl) {
-    for (int b = 0; b < (int)h->blocks.size(); ++b)
-      if (h->block_lane[b] == l) f(b, sl);
-  });
-}
 
-// A combined update of blocks [b0, b0 + n) of equal extents in the two-pass
-// form (see enqueue_combined_iteration).
-void tp_combined(mvd_handle* h, hipStream_t s, int b0, int n, int role, int conj_back, bool geo) {
+// A combined update of a set of blocks in the two-pass form (see
+// enqueue_combined_iteration).
+void tp_combined(mvd_handle* h, hipStream_t s, const mvd_handle::TpSet& set, int role, int conj_back, bool geo) {
   const int N = h->nviews;
   // the saved spectrum is the x passes': every view's plane pass reads it
-  for (int b = b0; b < b0 + n; ++b) {
+  for (int b : set.blocks) {
     const Block& B = h->blocks[b];
     HIPCHECK(hipMemcpyAsync(B.saved, B.spec, (size_t)(B.M + 1) * B.ny * B.nz * sizeof(float2),
                             hipMemcpyDeviceToDevice, s));
   }
   for (int v = 0; v < N; ++v) {
     const int opt = (v == 0 ? XOPT_FIRST : 0) | (geo ? XOPT_GEO : 0);
-    tp_launch_plane(h, s, b0, n, v, ROLE_P, 0, 1);
-    tp_launch_x(h, s, b0, n, 1, v, XOPT_SPEC);
-    tp_launch_plane(h, s, b0, n, v, role, conj_back, 0);
-    tp_launch_x(h, s, b0, n, v < N - 1 ? 3 : 4, v, opt | XOPT_SPEC);
+    tp_plane(h, s, set, v, ROLE_P, 0, 1);
+    tp_x(h, s, set, 1, v, XOPT_SPEC);
+    tp_plane(h, s, set, v, role, conj_back, 0);
+    tp_x(h, s, set, v < N - 1 ? 3 : 4, v, opt | XOPT_SPEC);
   }
 }
 
-// A combined update of block b alone on stream s, in the block's own form.
+// A combined update of block b alone on stream s, in the four passes.
 void enqueue_combined_block(mvd_handle* h, hipStream_t s, int variant, bool geo, int b) {
   const int role = variant == MVD_RL ? ROLE_P : variant;
   const int conj_back = variant == MVD_RL ? 1 : 0;
   const int N = h->nviews;
-  if (two_pass(h, b)) {
-    tp_combined(h, s, b, 1, role, conj_back, geo);
-    return;
-  }
   const Block& B = h->blocks[b];
   block_y(h, s, b, 0, 0);
   HIPCHECK(hipMemcpyAsync(B.saved, B.spec, B.spec_elems * 2 * sizeof(float), hipMemcpyDeviceToDevice, s));
@@ -2048,8 +2100,8 @@ void enqueue_combined_iteration(mvd_handle* h, hipStream_t s, int variant, bool 
   const int role = variant == MVD_RL ? ROLE_P : variant;
   const int conj_back = variant == MVD_RL ? 1 : 0;
   const int N = h->nviews;
-  if (h->spec_tp) {  // blocks of equal extents
-    tp_combined(h, s, 0, (int)h->blocks.size(), role, conj_back, geo);
+  if (h->spec_tp) {  // blocks on one lane
+    tp_combined(h, s, h->tp_lane[0], role, conj_back, geo);
     return;
   }
   run_y(h, s, 0, 0);
@@ -2113,14 +2165,11 @@ void prepare_run(mvd_handle* h, int variant, int n, bool classic = false) {
   h->stat_grid = two ? h->tp_tiles : h->grid_x;
   h->stat_parts = two ? h->d_tp_parts : h->d_parts;
   if ((!h->spec_valid || h->spec_tp != two) && !h->blocked) {
-    if (two && h->tp_even)
-      tp_launch_x(h, h->stream, 0, (int)h->blocks.size(), 0, 0, XOPT_SPEC);
-    else if (two)
-      over_blocks(h, h->stream, [&](int b, hipStream_t s) {
-        if (h->blocks[b].tpR)
-          tp_launch_x(h, s, b, 1, 0, 0, XOPT_SPEC);
-        else
-          block_x(h, s, b, 0, 0, nullptr, XOPT_SPEC);
+    if (two)
+      over_lanes(h, h->stream, [&](int l, hipStream_t s) {
+        tp_x(h, s, h->tp_lane[l], 0, 0, XOPT_SPEC);
+        for (int b = 0; b < (int)h->blocks.size(); ++b)
+          if (h->block_lane[b] == l && !h->blocks[b].tpR) block_x(h, s, b, 0, 0, nullptr, XOPT_SPEC);
       });
     else
       run_x(h, h->stream, 0, 0, nullptr, XOPT_SPEC);
@@ -2306,8 +2355,9 @@ void iterate_combined_impl(mvd_handle* h, int n, int variant, int mean) {
   const bool geo = mean == MVD_MEAN_GEOMETRIC;
   if (h->lanes.size() > 1) {
     run_lanes(h, lane_key(h, geo ? 1 : 2, variant, 1), n, [&](int l, hipStream_t s) {
+      if (h->spec_tp) tp_combined(h, s, h->tp_lane[l], variant == MVD_RL ? ROLE_P : variant, variant == MVD_RL, geo);
       for (int b = 0; b < (int)h->blocks.size(); ++b)
-        if (h->block_lane[b] == l) enqueue_combined_block(h, s, variant, geo, b);
+        if (h->block_lane[b] == l && !two_pass(h, b)) enqueue_combined_block(h, s, variant, geo, b);
     });
   } else if (replay(h)) {
     hipGraphExec_t ex = graph_for(h, variant, geo ? 1 : 2);
@@ -3225,8 +3275,8 @@ int mvd_view_update(mvd_handle* h, int view, int variant) {
     if (view < 0 || view >= h->nviews) bad("view index out of range");
     h->rec_token = 0;
     prepare_run(h, variant, 0);
-    if (h->spec_tp && !h->tp_even)
-      over_blocks(h, h->stream, [&](int b, hipStream_t s) { enqueue_view_block(h, s, variant, view, b); });
+    if (h->spec_tp)
+      over_lanes(h, h->stream, [&](int l, hipStream_t s) { enqueue_lane_view(h, s, variant, view, l); });
     else
       enqueue_view(h, h->stream, variant, view);
     finish_run(h);

@@ -294,3 +294,47 @@ def test_psfs_that_find_no_memory_leave_the_old_ones(mvd):
         # the failed call gave the two-pass form's memory back: four passes since
         d.iterate(2, "eff").set_tiles(*cfg).iterate(4, "eff")
         np.testing.assert_array_equal(out, d.estimate().cpu().numpy())
+
+
+@pytest.mark.parametrize("graphs", [False, True])
+def test_lanes_of_several_uneven_blocks(mvd, graphs):
+    """More blocks than lanes: a plane pass takes a lane's blocks of all
+    extents in one launch, an x pass those of one half-row and workgroup, and
+    four-pass blocks follow; every block keeps the bits it has alone."""
+    from oracle import mvd_oracle as O
+    rng = np.random.default_rng(905)
+    dims = [tuple(int(rng.choice(c)) for c in ((16, 20, 24, 32, 40, 48), (8, 12, 15, 24, 30), (9, 16, 25, 32)))
+            for _ in range(36)] + [(16, 3, 8), (540, 12, 10), (64, 64, 40)]
+    blocks = [problem(d, 2, 910 + i, False) for i, d in enumerate(dims)]
+    steps = [lambda d: d.iterate(2, "eff"), lambda d: d.iterate_combined(2, "rl", "geometric"),
+             lambda d: d.view_update(1, "eff")]
+    refs, flux = [], 0.0
+    for v, p, _ in blocks:
+        with mvd.Deconvolver(v, p) as d:
+            refs.append([f(d).estimate().cpu().numpy() for f in steps] + [d.two_pass_split()])
+            flux += np.array(d.stats()["flux"])
+    with mvd.Deconvolver.batch(blocks, use_graphs=graphs) as b:
+        for j, f in enumerate(steps):
+            f(b)
+            for i, r in enumerate(refs):
+                got = b.estimate(i).cpu().numpy()
+                if r[-1]:
+                    np.testing.assert_array_equal(got, r[j])
+                else:
+                    assert O.rel_l2(got, r[j]) <= 1e-5
+        np.testing.assert_allclose(b.stats()["flux"], flux, rtol=1e-6)
+
+
+def test_crowded_lanes_of_four_pass_blocks(mvd):
+    """Several small blocks of a lane without a two-pass form: the whole batch
+    takes the four passes."""
+    dims = [(32, 24, z) for z in (16, 18, 20)]
+    dims += [(4, 3, z) for z in (2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27, 30, 32, 36, 40)]
+    blocks = [problem(d, 1, 950 + i, False) for i, d in enumerate(dims)]
+    with mvd.Deconvolver.batch(blocks) as b:
+        b.iterate(2, "rl")
+        assert not any(b.two_pass_split(i) for i in range(len(dims)))
+        for i, (v, p, _) in enumerate(blocks):
+            with mvd.Deconvolver(v, p) as d:
+                np.testing.assert_allclose(b.estimate(i).cpu().numpy(), d.iterate(2, "rl").estimate().cpu().numpy(),
+                                           rtol=1e-4)
