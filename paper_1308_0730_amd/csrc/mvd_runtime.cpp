@@ -2353,7 +2353,7 @@ void iterate_combined_impl(mvd_handle* h, int n, int variant, int mean) {
   ensure_combined(h);
   prepare_run(h, variant, n);
   const bool geo = mean == MVD_MEAN_GEOMETRIC;
-  if (h->lanes.size() > 1) {
+  if (h->lanes.size() > 1 && (h->spec_tp || per_length_plans(h))) {
     run_lanes(h, lane_key(h, geo ? 1 : 2, variant, 1), n, [&](int l, hipStream_t s) {
       if (h->spec_tp) tp_combined(h, s, h->tp_lane[l], variant == MVD_RL ? ROLE_P : variant, variant == MVD_RL, geo);
       for (int b = 0; b < (int)h->blocks.size(); ++b)
