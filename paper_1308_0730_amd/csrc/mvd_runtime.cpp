@@ -2792,11 +2792,11 @@ void set_psfs_impl(mvd_handle* h, const float* const* psfs, const int* psf_dims,
     dims.push_back({k[0], k[1], k[2]});
   }
   HIPCHECK(hipStreamSynchronize(h->stream));
-  Block W = B;  // with the new window; the handle keeps the old PSFs if there is no memory for it
-  W.P = P;
-  set_kernel_window(W);
+  // the handle keeps the old PSFs if there is no memory for a wider window
+  int kz = 1;
+  for (const auto& K : P) kz = std::max(kz, K.kz);
   float* H = nullptr;
-  if (W.kz > B.kz_cap) H = (float*)h->dalloc((size_t)N * W.h_elems * 2 * sizeof(float));
+  if (kz > B.kz_cap) H = (float*)h->dalloc((size_t)N * (B.Mp + 1) * B.ny * kz * 2 * sizeof(float));
   B.P = std::move(P);
   B.psf_sum = std::move(sums);
   B.psf_dims = std::move(dims);

@@ -242,7 +242,7 @@ class Deconvolver:
             # block in the order of the stream it was allocated on only (at
             # create the handle's stream is the current one)
             try:
-                if self._h is None or torch.cuda.current_stream(dev) == self.stream:
+                if self._h is None or torch.cuda.current_stream(dev.index) == self.stream:
                     t = torch.empty(int(nbytes), dtype=torch.uint8, device=dev)
                 else:
                     with torch.cuda.stream(self.stream):
